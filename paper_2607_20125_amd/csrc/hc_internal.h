@@ -87,21 +87,27 @@ struct ScatterArgs {
   uint8_t head_slot[kMaxHeads];
 };
 
+// Token rows per work group of the statistics kernel, and its groups per head.
+constexpr int kClsStatRows = 64;
+inline int cls_stat_groups(int L) { return (L + kClsStatRows - 1) / kClsStatRows; }
+
 struct StatsArgs {
   const float *o_ref, *o_sink, *o_dummy, *o_sp;   // [H][L][d]
-  double *out;                                     // [H][L][4]
-  int32_t n_rows;                                  // H * L
-  int32_t D;
+  double *cos_sp;                                  // [H][L] cos(spatial, ref)
+  // [H][cls_stat_groups(L)][4]: sums over the group's rows of cos(sink, ref),
+  // cos(dummy, ref), cos(spatial, ref) and |sp - ref|^2
+  double *sums;
+  int32_t n_heads, L, D;
 };
 
-// Per-head statistics of Eq. 3 and Eq. 4 from the per-token ones: out[h][0..5] =
+// Per-head statistics of Eq. 3 and Eq. 4 from the token ones: out[h][0..5] =
 // mean cos(sink, ref), mean cos(dummy, ref), mean cos(spatial, ref), the 5th
 // percentile of cos(spatial, ref) (linear interpolation at rank 0.05 (L - 1)),
 // MSE = sum (sp - ref)^2 / (L d), score = P5 - gamma MSE.  One work group per head.
 struct ClsReduceArgs {
-  const double *tok;       // [H][L][4] from the statistics kernel
-  double *out;             // [H][6]
-  int32_t n_heads, L, D;
+  const double *cos_sp, *sums;   // from the statistics kernel
+  double *out;                   // [H][6]
+  int32_t n_heads, n_groups, L, D;
   double gamma;
 };
 

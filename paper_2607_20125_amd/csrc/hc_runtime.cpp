@@ -926,19 +926,21 @@ hc_status hc_classify_heads(hc_ctx *c, int layer, int64_t cur_block, const void 
   }
   // 3. per-token and then per-head statistics on the device (float64), the
   // decision on the host
-  if ((st = keep(c, c->cls_tok, ((size_t)H * L * 4 + (size_t)H * HC_N_STATS) * sizeof(double))) !=
-      HC_OK)
+  const int groups = cls_stat_groups(L);
+  if ((st = keep(c, c->cls_tok, (size_t)H * (L + groups * 4 + HC_N_STATS) * sizeof(double))) != HC_OK)
     return st;
-  double *tok = (double *)c->cls_tok.p;
-  double *head_stats = tok + (size_t)H * L * 4;
+  double *cos_sp = (double *)c->cls_tok.p;
+  double *sums = cos_sp + (size_t)H * L;
+  double *head_stats = sums + (size_t)H * groups * 4;
   {
     StatsArgs a{};
     a.o_ref = o_ref; a.o_sink = o_sink; a.o_dummy = o_dum; a.o_sp = o_sp;
-    a.out = tok; a.n_rows = H * L; a.D = D;
+    a.cos_sp = cos_sp; a.sums = sums; a.n_heads = H; a.L = L; a.D = D;
     st = timed_launch(c, s, HC_K_STATS, [&] { return launch_stats(a, s); });
     if (st != HC_OK) return st;
     ClsReduceArgs r{};
-    r.tok = tok; r.out = head_stats; r.n_heads = H; r.L = L; r.D = D;
+    r.cos_sp = cos_sp; r.sums = sums; r.out = head_stats;
+    r.n_heads = H; r.n_groups = groups; r.L = L; r.D = D;
     r.gamma = (double)c->cfg.gamma;
     st = timed_launch(c, s, HC_K_STATS, [&] { return launch_cls_reduce(r, s); });
     if (st != HC_OK) return st;

@@ -69,3 +69,33 @@ def test_classify_outputs_480p_sampled_rows(hc):
     every output on stratified rows of three heads."""
     w = S.WORKLOADS["480p"]
     _check_outputs(hc, w, heads=(0, 5, 11), rows=stratified_rows(w))
+
+
+@pytest.mark.parametrize("grid_h, grid_w, frames, d, kind", [
+    (1, 8, 1, 64, "normal"),       # fewer rows than one group of the statistics kernel
+    (8, 9, 1, 128, "normal"),      # one row past a group
+    (24, 45, 2, 64, "normal"),     # more rows than threads of the reduction, cosines of both signs
+    (24, 45, 2, 128, "constant"),  # V constant: all cosines tie or differ in the last bits
+    (16, 20, 1, 128, "zero"),      # V zero: every cosine is 0 over the 1e-30 floor
+])
+def test_statistics_of_the_outputs(hc, grid_h, grid_w, frames, d, kind):
+    """The six statistics are exactly Eq. 3 and Eq. 4 of the four outputs: both
+    sides are float64 on the same float32 values, so they differ by the order of
+    sums only (L d terms of 2^-53 each; the percentile is an order statistic)."""
+    w = S.Workload("stat", 1, 4, d, grid_h, grid_w, frames, 3, 1, 1, 5, (1, 1, 1, 1))
+    cur = w.window_blocks - 1
+    q, k, v = S.gen_layer(w, 0, cur)
+    if kind == "constant":
+        v = np.broadcast_to(v[:, :1], v.shape)
+    elif kind == "zero":
+        v = np.zeros_like(v)
+    ctx = hc.Context(hc.config_from_workload(w), 0)
+    _, stats = ctx.classify_heads(0, cur, dev_bf16(q), dev_bf16(k), dev_bf16(v))
+    outs = []
+    for _, name in OUTPUTS:
+        o = _empty(w)
+        ctx.classify_outputs(getattr(hc, name), o)
+        outs.append(o.cpu().numpy().astype(np.float64))
+    for h in range(w.n_heads):
+        ref = O.head_statistics(*(o[h] for o in outs))
+        np.testing.assert_allclose(stats[h], ref, rtol=1e-12, atol=1e-13, err_msg=f"head {h}")
