@@ -165,9 +165,10 @@ void hc_destroy(hc_ctx *ctx);   /* NULL is allowed; synchronises the device firs
  * hc_set_head_types would.  SYNCHRONISES `stream` (the labels are host
  * outputs).  Needs device memory of about 2 * H*W*L*d*2 bytes (the window in
  * Global layout) + the window in Spatial layout (rows padded to a multiple of 8
- * keys) + 4 * H*L*d*4 bytes
- * (the proxy outputs) + the per-block partials (H*W*ceil(L/128) slots of
- * 128*(d+2) floats) + the token statistics (about H*L doubles): the first call allocates it, the context keeps it for
+ * keys) unless grid_w is a multiple of 8 + 4 * H*L*d*4 bytes (the proxy
+ * outputs) + the per-block partials (H*W*ceil(L/128) slots of 128*(d+2) floats)
+ * + the token statistics (about H*L doubles): the first call allocates it, the
+ * context keeps it for
  * later calls (every layer of a generation) and releases it in hc_destroy;
  * hc_memory_bytes counts it. */
 hc_status hc_classify_heads(hc_ctx *ctx, int layer, int64_t cur_block, const void *q,

@@ -7,27 +7,37 @@ namespace {
 using namespace dev;
 
 // ---------------------------------------------------------------------------
-// Scatter: one work group = 64 tokens of one (head, source block).
+// Scatter: one work group = 64 rows of one (head, source block), 64 tokens or,
+// for the frames of a Spatial buffer, 64 storage keys.
 // K rows are copied as 16-byte chunks; V goes through LDS and is written in the
-// 8-key-grouped layout, 16 bytes per (8 keys, dim) when the 8 keys are one
-// aligned group, else element by element.
+// 8-key-grouped layout, 16 bytes per (8 keys, dim) when the 8 rows are one
+// aligned group, else element by element.  A Spatial frame is walked by its
+// storage (rows of `pitch` keys) and not by its tokens, because then every
+// group of eight is aligned also where grid_w is not a multiple of 8: the
+// padding columns of a row are read as zeros and written as such.  By tokens,
+// three of four groups of a 52-wide grid went out as single elements: all-head
+// split of a 480P window 95 -> 78 us, append of a routed
+// 480P layer with three Spatial heads 16.4 -> 15.0 us.
 // ---------------------------------------------------------------------------
 template <int D>
 __global__ __launch_bounds__(256) void kv_scatter_kernel(ScatterArgs a) {
   constexpr int TT = 64;
   constexpr int VS = D + 8;
   __shared__ __attribute__((aligned(16))) uint16_t sV[TT * VS];
-  const int ntt = (a.L + TT - 1) / TT;
+  // source token (-1: none) and destination key (-1: past the end) of every row,
+  // computed once (the Spatial layouts need integer divisions)
+  __shared__ int64_t skey[TT];
+  __shared__ int stok[TT];
   int bid = blockIdx.x;
-  const int tt = bid % ntt;
-  bid /= ntt;
+  const int tt = bid % a.n_tiles;
+  bid /= a.n_tiles;
   const int i = bid % a.n_src;
   const int h = bid / a.n_src;
 
   const uint8_t kind = a.head_kind[h];
   uint16_t *kd, *vd;
   int64_t kph;      // keys per head of the destination buffer
-  int mode;         // 0 dense rows, 1 spatial rows
+  int mode;         // 0 dense rows, 1 Spatial frames, 2 cells
   int64_t kbase = 0;
   if (kind == 0 /*sink*/ || kind == 1 /*dummy*/) {
     const int sd = kind == 0 ? a.sink_slot[i] : a.dummy_slot[i];
@@ -38,53 +48,64 @@ __global__ __launch_bounds__(256) void kv_scatter_kernel(ScatterArgs a) {
     kd = a.k_g; vd = a.v_g; kph = a.g_keys; mode = 0;
     kbase = (int64_t)a.src_slot[i] * a.L;
   } else {
-    kd = a.k_sp; vd = a.v_sp; kph = a.sp_keys; mode = 1;
+    kd = a.k_sp; vd = a.v_sp; kph = a.sp_keys; mode = a.cell > 0 ? 2 : 1;
   }
+  const int slot = a.src_slot[i];
+  const int t0 = tt * TT;
+  const int frame_keys = a.geo.rows * a.geo.pitch;
+  const int n_rows = mode == 1 ? a.F * frame_keys : a.L;
+  if (t0 >= n_rows) return;
   const int64_t hoff = (int64_t)a.head_slot[h] * kph * D;
   kd += hoff;
   vd += hoff;
-  const int slot = a.src_slot[i];
-  const int P = a.Hg * a.Wg;
-  auto key_of = [&](int tok) -> int64_t {
-    if (mode == 0) return kbase + tok;
-    const int fr = tok / P, p = tok % P;
-    const int yy = p / a.Wg, xx = p % a.Wg;
-    if (a.cell > 0) {
-      const int cy = min(yy / a.cell, a.ncy - 1), cx = min(xx / a.cell, a.ncx - 1);
-      const int ch = cy == a.ncy - 1 ? a.Hg - cy * a.cell : a.cell;
-      const int cw = cx == a.ncx - 1 ? a.Wg - cx * a.cell : a.cell;
-      return a.cell_off[cy * a.ncx + cx] + ((int64_t)slot * a.F + fr) * ch * cw +
-             (yy - cy * a.cell) * cw + (xx - cx * a.cell);
+  if (threadIdx.x < TT) {
+    const int row = t0 + threadIdx.x;
+    const int P = a.Hg * a.Wg;
+    int tok = row < n_rows ? row : -1;
+    int64_t key = -1;
+    if (tok >= 0) {
+      if (mode == 0) {
+        key = kbase + tok;
+      } else if (mode == 1) {
+        const int fr = row / frame_keys, p = row % frame_keys;
+        const int yy = p / a.geo.pitch, xx = p % a.geo.pitch;
+        key = (int64_t)slot * a.F * frame_keys + row;
+        tok = xx < a.Wg ? fr * P + yy * a.Wg + xx : -1;
+      } else {
+        const int fr = tok / P, p = tok % P;
+        const int yy = p / a.Wg, xx = p % a.Wg;
+        const int cy = min(yy / a.cell, a.ncy - 1), cx = min(xx / a.cell, a.ncx - 1);
+        const int ch = cy == a.ncy - 1 ? a.Hg - cy * a.cell : a.cell;
+        const int cw = cx == a.ncx - 1 ? a.Wg - cx * a.cell : a.cell;
+        key = a.cell_off[cy * a.ncx + cx] + ((int64_t)slot * a.F + fr) * ch * cw +
+              (yy - cy * a.cell) * cw + (xx - cx * a.cell);
+      }
     }
-    return (((int64_t)slot * a.F + fr) * a.geo.rows + a.geo.y0 + yy) * a.geo.pitch + a.geo.x0 + xx;
-  };
+    stok[threadIdx.x] = tok;
+    skey[threadIdx.x] = key;
+  }
 
-  const int t0 = tt * TT;
   const uint16_t *sk = a.src_k + ((size_t)(h * a.n_src + i) * a.L) * D;
   const uint16_t *sv = a.src_v + ((size_t)(h * a.n_src + i) * a.L) * D;
-  // destination key of every token of the group, computed once (the Spatial
-  // layouts need integer divisions)
-  __shared__ int64_t skey[TT];
-  if (threadIdx.x < TT) skey[threadIdx.x] = t0 + threadIdx.x < a.L ? key_of(t0 + threadIdx.x) : -1;
   __syncthreads();
   constexpr int CPR = D / 8;
   for (int c = threadIdx.x; c < TT * CPR; c += 256) {
     const int lt = c / CPR, col = c % CPR;
-    const int tok = t0 + lt;
-    if (tok < a.L) {
+    const int tok = stok[lt];
+    u32x4 vv = {0, 0, 0, 0};
+    if (tok >= 0) {
       const u32x4 kv = *reinterpret_cast<const u32x4 *>(sk + (size_t)tok * D + col * 8);
       *reinterpret_cast<u32x4 *>(kd + skey[lt] * D + col * 8) = kv;
-      *reinterpret_cast<u32x4 *>(&sV[lt * VS + col * 8]) =
-          *reinterpret_cast<const u32x4 *>(sv + (size_t)tok * D + col * 8);
+      vv = *reinterpret_cast<const u32x4 *>(sv + (size_t)tok * D + col * 8);
     }
+    *reinterpret_cast<u32x4 *>(&sV[lt * VS + col * 8]) = vv;
   }
   __syncthreads();
   for (int w = threadIdx.x; w < D * (TT / 8); w += 256) {
     const int d = w % D, j = w / D;
-    const int tokA = t0 + 8 * j;
-    if (tokA >= a.L) continue;
     const int64_t kA = skey[8 * j];
-    const bool full = tokA + 7 < a.L && (kA & 7) == 0 && skey[8 * j + 7] == kA + 7;
+    if (kA < 0) continue;
+    const bool full = (kA & 7) == 0 && skey[8 * j + 7] == kA + 7;
     if (full) {
       uint16_t vals[8];
 #pragma unroll
@@ -94,7 +115,7 @@ __global__ __launch_bounds__(256) void kv_scatter_kernel(ScatterArgs a) {
       for (int e = 0; e < 4; ++e) pk[e] = (uint32_t)vals[2 * e] | ((uint32_t)vals[2 * e + 1] << 16);
       *reinterpret_cast<u32x4 *>(vd + ((kA >> 3) * D + d) * 8) = pk;
     } else {
-      for (int e = 0; e < 8 && tokA + e < a.L; ++e) {
+      for (int e = 0; e < 8 && skey[8 * j + e] >= 0; ++e) {
         const int64_t ke = skey[8 * j + e];
         vd[((ke >> 3) * D + d) * 8 + (ke & 7)] = sV[(8 * j + e) * VS + d];
       }
@@ -353,9 +374,14 @@ hipError_t launch_cls_reduce(const ClsReduceArgs &a, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_scatter(const ScatterArgs &a, int n_heads, hipStream_t s) {
-  const int ntt = (a.L + 63) / 64;
-  dim3 grid((unsigned)(n_heads * a.n_src * ntt)), block(256);
+hipError_t launch_scatter(ScatterArgs a, int n_heads, hipStream_t s) {
+  // tiles of 64 rows per (head, block): a Spatial frame's storage has at least
+  // as many rows as tokens
+  bool frames = false;
+  for (int h = 0; h < n_heads; ++h) frames |= a.head_kind[h] == HC_SPATIAL;
+  const int rows = frames && a.cell == 0 ? a.F * a.geo.rows * a.geo.pitch : a.L;
+  a.n_tiles = (rows + 63) / 64;
+  dim3 grid((unsigned)(n_heads * a.n_src * a.n_tiles)), block(256);
   if (a.D == 128)
     hipLaunchKernelGGL((kv_scatter_kernel<128>), grid, block, 0, s, a);
   else

@@ -67,6 +67,7 @@ struct ScatterArgs {
   const uint16_t *src_k;   // [H][n_src * L][d]
   const uint16_t *src_v;
   int32_t n_src;
+  int32_t n_tiles;         // 64-row tiles per (head, block)
   int32_t L, D, Hg, Wg, F;
   SpatialGeom geo;         // layout of the Spatial buffer (centred-window variant)
   // cell variant (cell > 0): the Spatial buffer is cell-major; cell (cy, cx) of
@@ -120,7 +121,7 @@ hipError_t launch_combine(const CombineArgs &a, hipStream_t s);
 // The role only separates kernel symbols by caller, as for the dense kernel.
 enum class SpatialRole { kRouted, kClassify, kSpatialOnly };
 hipError_t launch_spatial(const SpatialArgs &a, int head_dim, SpatialRole role, hipStream_t s);
-hipError_t launch_scatter(const ScatterArgs &a, int n_heads, hipStream_t s);
+hipError_t launch_scatter(ScatterArgs a, int n_heads, hipStream_t s);   // sets n_tiles
 hipError_t launch_stats(const StatsArgs &a, hipStream_t s);
 hipError_t launch_cls_reduce(const ClsReduceArgs &a, hipStream_t s);
 

@@ -71,6 +71,15 @@ def test_classify_outputs_480p_sampled_rows(hc):
     _check_outputs(hc, w, heads=(0, 5, 11), rows=stratified_rows(w))
 
 
+@pytest.mark.parametrize("grid_w, proxy", [(16, 0), (16, 6), (24, 3), (13, 2), (13, 9)])
+def test_classify_outputs_frame_storage(hc, grid_w, proxy):
+    """The Spatial proxy reads the Global copy of the window where a frame has no
+    padding columns (16, 24) and a copy with padded rows where it has (13): halos
+    reach past the first and the last frame of every head."""
+    w = S.Workload("proxy", 1, 4, 64, 9 if grid_w != 13 else 8, grid_w, 2, 3, 1, proxy, 6, (1, 1, 1, 1))
+    _check_outputs(hc, w, heads=range(w.n_heads))
+
+
 @pytest.mark.parametrize("grid_h, grid_w, frames, d, kind", [
     (1, 8, 1, 64, "normal"),       # fewer rows than one group of the statistics kernel
     (8, 9, 1, 128, "normal"),      # one row past a group
