@@ -10,8 +10,9 @@ using namespace dev;
 
 // ---------------------------------------------------------------------------
 // Dense kernel: one work group = kQTile (128) queries of one unit on 4 waves of
-// 32 queries; two work groups share a CU (two waves per SIMD, 2 x 80 KB of LDS),
-// so one group's barrier waits and softmax overlap the other's matrix work.
+// 32 queries; two work groups share a CU (two waves per SIMD, 2 x 80 KB of LDS;
+// three with 64-dim heads), so one group's barrier waits and softmax overlap the
+// others' matrix work.
 // K/V tiles of 64 keys are fetched kDist tiles ahead of use (K ring of kDist,
 // V ring of kDist + 1 buffers); one barrier per tile.
 // The key loop is software-pipelined inside each wave: while the matrix cores
@@ -28,7 +29,7 @@ constexpr int kDist = 2;
 // 1 full-window step (all heads Global), 2 classification, 3 routed step of a
 // context with the cell or two-block variant, 4 a table of Sink and Dummy heads only.
 template <int D, int kRole>
-__global__ __launch_bounds__(64 * kDenseWaves, 2) void attn_dense_kernel(DenseArgs a) {
+__global__ __launch_bounds__(64 * kDenseWaves, dense_groups_per_cu(D)) void attn_dense_kernel(DenseArgs a) {
   constexpr int NW = kDenseWaves;            // waves per work group
   constexpr int KT = kKTile;
   constexpr int NKK = D / 16;
@@ -40,7 +41,7 @@ __global__ __launch_bounds__(64 * kDenseWaves, 2) void attn_dense_kernel(DenseAr
   constexpr int RK = kDist, RV = kDist + 1;  // ring buffers
   static_assert(LPW >= 1, "tile too small for the wave count");
   static_assert(kDist >= 2 && kDist <= 4, "prefetch distance");
-  static_assert((RK + RV) * TILE * 2 <= 80 * 1024, "LDS: two work groups per CU");
+  static_assert((RK + RV) * TILE * 2 * dense_groups_per_cu(D) <= 160 * 1024, "LDS of a CU");
   __shared__ __attribute__((aligned(1024))) uint16_t sK[RK][TILE];
   __shared__ __attribute__((aligned(1024))) uint16_t sV[RV][TILE];
 
@@ -272,18 +273,24 @@ __global__ __launch_bounds__(64 * kDenseWaves, 2) void attn_dense_kernel(DenseAr
         // products of the 16-key chunks whose probabilities are done.  Measured
         // against five per S(t+1) product and none after: 2-4% faster; none
         // during S(t+1) was slower, as was leaving the order to the scheduler.
+        // With 64-dim heads a tile has half the products for the same softmax:
+        // three vector instructions per S(t+1) product (8 of them), up to five
+        // per PV and row-sum product (12).  Together with the third work group
+        // per CU 505 -> 463 us for 16 full-window heads of 25392 keys (476 us
+        // with two groups; 466 with three and the compiler's order).
+        constexpr int kSV = D == 64 ? 3 : 1, kPV = D == 64 ? 5 : 3;
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);     // DS reads
 #pragma unroll
-        for (int i = 0; i < 16; ++i) {
+        for (int i = 0; i < 2 * NKK; ++i) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);   // MFMA
           __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x002, 1, 0);   // VALU
+          __builtin_amdgcn_sched_group_barrier(0x002, kSV, 0); // VALU
         }
 #pragma unroll
-        for (int i = 0; i < 20; ++i) {
+        for (int i = 0; i < 4 * (NDB + 1); ++i) {
           __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
           __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-          __builtin_amdgcn_sched_group_barrier(0x002, 3, 0);
+          __builtin_amdgcn_sched_group_barrier(0x002, kPV, 0);
         }
       }
     };

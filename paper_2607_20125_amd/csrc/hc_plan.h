@@ -91,12 +91,14 @@ struct DensePlanShape {
 // block exists, merged like a Global head), cells one query-mapped unit per
 // 128 queries of a cell.  Units are ordered (head, key block, query tile) so
 // that neighbouring units read the same K/V.  Then tail-balanced for n_cu CUs.
-inline void balance_units(int n_cu, std::vector<DenseUnit> &units, std::vector<CombineItem> &comb);
+inline void balance_units(int n_cu, std::vector<DenseUnit> &units, std::vector<CombineItem> &comb,
+                          int groups_per_cu = 2);
 
 inline void plan_dense_units(const DensePlanShape &s, const std::vector<HeadKV> &global,
                              const std::vector<HeadKV> &sink_dummy,
                              const std::vector<HeadKV> &cell_heads, int n_cu,
-                             std::vector<DenseUnit> &units, std::vector<CombineItem> &comb) {
+                             std::vector<DenseUnit> &units, std::vector<CombineItem> &comb,
+                             int groups_per_cu = 2) {
   const int L = s.L, nv = s.nv;
   const int nqt = (L + kQTile - 1) / kQTile;
   units.clear();
@@ -152,7 +154,7 @@ inline void plan_dense_units(const DensePlanShape &s, const std::vector<HeadKV> 
           }
         }
   }
-  balance_units(n_cu, units, comb);
+  balance_units(n_cu, units, comb, groups_per_cu);
 }
 
 // ---------------------------------------------------------------------------
@@ -297,7 +299,7 @@ inline int first_unit_outside(const std::vector<DenseUnit> &units,
 // ---------------------------------------------------------------------------
 // Tail balancing of a dense launch.  Work groups are dealt round-robin to the
 // 8 XCDs and the kernel maps them so that XCD x runs a contiguous run of the
-// unit list in order, `per_xcd` (two per CU) at a time.  With equal units the
+// unit list in order, `groups_per_cu` per CU at a time (dense_groups_per_cu).  With equal units the
 // last round of a run is partly empty.  For each run, the tail (its last
 // partial round, or that plus one full round) is cut into pieces of whole key
 // tiles when a list-scheduling simulation says the run then ends earlier; each
@@ -349,13 +351,20 @@ struct SlotClock {
   }
 };
 
+// Pieces a unit of a cut suffix is cut into when k are asked for: none if they
+// would have fewer than kMinPieceTiles tiles each.
+inline int unit_pieces(const DenseUnit &u, int k) {
+  return u.qn == 0 && unit_tiles(u) >= k * kMinPieceTiles ? k : 1;
+}
+
 // How the run [b, e) of the unit list is cut: the suffix length *best_j and the
 // pieces *best_k per unit of it that end the run earliest by at least 1%, else
 // 0 and 1.  The uncut units before a suffix are simulated once: the clock is
 // copied where a suffix starts and each number of pieces continues from the
-// copy, until it is past the best end so far.
-inline void best_cut(const std::vector<DenseUnit> &units, int b, int e, int slots, int *best_j,
-                     int *best_k) {
+// copy, until it is past the best end so far.  `most` (or null): the pieces each
+// unit may have.
+inline void best_cut(const std::vector<DenseUnit> &units, const int *most, int b, int e, int slots,
+                     int *best_j, int *best_k) {
   const int tail = (e - b) % slots;
   SlotClock clock(slots), at_long = clock, at_short = clock;
   for (int i = b; i < e; ++i) {
@@ -372,8 +381,7 @@ inline void best_cut(const std::vector<DenseUnit> &units, int b, int e, int slot
       SlotClock cl = j == tail ? at_short : at_long;
       for (int i = e - j; i < e && cl.end < best * 0.99; ++i) {
         const int nt = unit_tiles(units[i]);
-        const bool can = units[i].qn == 0 && nt >= k * kMinPieceTiles;
-        const int kk = can ? k : 1;
+        const int kk = unit_pieces(units[i], most ? std::min(k, most[i]) : k);
         for (int p = 0; p < kk; ++p)
           cl.add((nt * (p + 1) / kk - nt * p / kk) + kUnitOverheadTiles);
       }
@@ -385,11 +393,12 @@ inline void best_cut(const std::vector<DenseUnit> &units, int b, int e, int slot
 }  // namespace plan_detail
 
 // n_cu: compute units of the device (a multiple of 8; otherwise the list is left as is).
-inline void balance_units(int n_cu, std::vector<DenseUnit> &units, std::vector<CombineItem> &comb) {
+inline void balance_units(int n_cu, std::vector<DenseUnit> &units, std::vector<CombineItem> &comb,
+                          int groups_per_cu) {
   using namespace plan_detail;
   const int n = (int)units.size();
   if (n_cu <= 0 || n_cu % 8 != 0 || n == 0) return;
-  const int slots = 2 * n_cu / 8;
+  const int slots = groups_per_cu * n_cu / 8;
   // item of every unit: the combine item holding its slot, or -1 (writes o)
   std::vector<int> item(n, -1);
   {
@@ -405,6 +414,10 @@ inline void balance_units(int n_cu, std::vector<DenseUnit> &units, std::vector<C
   }
   std::vector<int> item_n(comb.size());
   for (size_t i = 0; i < comb.size(); ++i) item_n[i] = comb[i].n_slots;
+  // pieces per unit that an item of at most kMaxSrcBlocks slots has room for when
+  // all its units are cut
+  std::vector<int> most(n);
+  for (int i = 0; i < n; ++i) most[i] = item[i] < 0 ? kMaxSrcBlocks : kMaxSrcBlocks / item_n[item[i]];
 
   struct Piece { DenseUnit u; int item; };
   std::vector<std::vector<Piece>> runs(8);
@@ -423,14 +436,34 @@ inline void balance_units(int n_cu, std::vector<DenseUnit> &units, std::vector<C
     };
     bool again = m == prev_e - prev_b;
     for (int i = 0; again && i < m; ++i) again = same(b + i, prev_b + i);
-    if (!again) best_cut(units, b, e, slots, &best_j, &best_k);
+    if (!again) best_cut(units, nullptr, b, e, slots, &best_j, &best_k);
     prev_b = b;
     prev_e = e;
+    // where an item has no room for its units' pieces, the run is cut again with
+    // the room shared out evenly: giving it out first come first served left
+    // single units whole at the end of a run (up to 1.9x the run's uncut time)
+    int cut_j = best_j, cut_k = best_k;
+    const int *limit = nullptr;
+    auto grow = [&](int sign) {
+      bool fits = true;
+      for (int i = e - cut_j; i < e; ++i)
+        if (item[i] >= 0) {
+          item_n[item[i]] += sign * (unit_pieces(units[i], cut_k) - 1);
+          fits = fits && item_n[item[i]] <= kMaxSrcBlocks;
+        }
+      return fits;
+    };
+    const bool fits = grow(1);
+    grow(-1);
+    if (!fits) {
+      limit = most.data();
+      best_cut(units, limit, b, e, slots, &cut_j, &cut_k);
+    }
     std::vector<Piece> &r = runs[x];
     for (int i = b; i < e; ++i) {
       const DenseUnit &u = units[i];
       const int nt = unit_tiles(u);
-      int k = (i >= e - best_j && u.qn == 0 && nt >= best_k * kMinPieceTiles) ? best_k : 1;
+      int k = i >= e - cut_j ? unit_pieces(u, limit ? std::min(cut_k, limit[i]) : cut_k) : 1;
       if (k > 1 && item[i] >= 0 && item_n[item[i]] + k - 1 > kMaxSrcBlocks) k = 1;
       if (k == 1) { r.push_back({u, item[i]}); continue; }
       int it = item[i];

@@ -313,7 +313,8 @@ void plan_units(const hc_ctx *c, const Layer &l, int nv, std::vector<DenseUnit> 
       c->cfg.spatial_cell > 0 ? parts(l.sp_heads, l.k_sp, l.v_sp, c->cells.keys)
                               : std::vector<HeadKV>{};
   plan_dense_units(shape, parts(l.g_heads, l.k_g, l.v_g, c->g_keys),
-                   parts(l.sd_heads, l.k_sd, l.v_sd, c->sd_keys), cell_heads, c->n_cu, units, comb);
+                   parts(l.sd_heads, l.k_sd, l.v_sd, c->sd_keys), cell_heads, c->n_cu, units, comb,
+                   dense_groups_per_cu(D));
 }
 
 template <class T>

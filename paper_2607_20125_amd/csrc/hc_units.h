@@ -17,6 +17,11 @@ constexpr int kMaxSrcBlocks = 32;
 constexpr int kQTile = 128;    // queries per dense work unit (4 waves x 32)
 constexpr int kKTile = 64;     // keys per dense KV tile
 
+// Work groups of the dense kernel that share a CU: two by the registers of
+// 128-dim heads (224 of 256) and their 80 KB rings; 64-dim heads need half the
+// LDS and 168 registers, so three (four would need 128).
+inline constexpr int dense_groups_per_cu(int d) { return d == 64 ? 3 : 2; }
+
 // One dense work unit: kQTile queries of one head against the contiguous key range
 // [kv0, kv1) of a [keys][d] K buffer and its 8-key-grouped V buffer
 // ([keys/8][d][8]).  Every unit covers at most one window block of keys, so all

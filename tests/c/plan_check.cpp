@@ -61,13 +61,13 @@ static void build(const Layer &ly, std::vector<DenseUnit> &units, std::vector<Co
 using Key = std::tuple<int, int, int>;   // head, q0, qn
 static Key key_of(const DenseUnit &u) { return Key{u.head, u.q0, u.qn}; }
 
-static void check_layer(const Layer &ly, int n_cu, bool expect_cut) {
+static void check_layer(const Layer &ly, int n_cu, bool expect_cut, int groups = 2) {
   std::vector<DenseUnit> units, units0;
   std::vector<CombineItem> comb, comb0;
   build(ly, units, comb);
   units0 = units;
   comb0 = comb;
-  balance_units(n_cu, units, comb);
+  balance_units(n_cu, units, comb, groups);
   const int n = (int)units.size();
   // 1. equal runs, one per XCD, padding only at the end of a run (the list is
   //    left as it is when the CU count is not a multiple of 8)
@@ -148,7 +148,7 @@ static void check_layer(const Layer &ly, int n_cu, bool expect_cut) {
   CHECK(comb.size() >= comb0.size(), "items lost");
   // 6. simulated end time does not grow
   auto makespan = [&](const std::vector<DenseUnit> &us) {
-    const int m = (int)us.size(), slots = 2 * n_cu / 8;
+    const int m = (int)us.size(), slots = groups * n_cu / 8;
     double worst = 0;
     const int p8 = m / 8, r8 = m % 8;
     for (int x = 0; x < 8; ++x) {
@@ -330,6 +330,7 @@ int main() {
       const bool expect = n_cu == 256 && ((ly.L == 4680 && ly.n_g == 2 && ly.n_sd == 0) ||
                                           (ly.L == 4680 && ly.n_g == 1 && ly.n_sd == 1));
       check_layer(ly, n_cu, expect);
+      check_layer(ly, n_cu, false, 3);   // three work groups per CU (64-dim heads)
     }
   if (failures) {
     std::printf("plan_check: %d failures\n", failures);

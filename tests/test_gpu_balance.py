@@ -31,3 +31,23 @@ def test_balanced_tail_480p(hc, types):
     ref = O.routed_attention(types, q, k, v, w.grid_h, w.grid_w, w.frames_per_block,
                              w.spatial_radius)
     assert_close(o.cpu().numpy(), ref, f"balanced tail types={types.tolist()}")
+
+
+@pytest.mark.parametrize("types", [(0, 3), (3, 3), (1, 3, 3, 3)])
+def test_balanced_tail_64_dim_heads(hc, types):
+    """64-dim heads: three work groups share a CU, so the runs are cut for 96 slots per
+    XCD; the tile loop ends on every remainder modulo its unrolling (L = 2376 = 37 tiles
+    and 8 keys, cut into pieces of 12 tiles or more)."""
+    import torch
+    types = np.array(types, np.uint8)
+    w = S.Workload("bal64", 1, len(types), 64, 22, 36, 3, 5, 4, 2, 482, (0, 0, 0, len(types)))
+    cur = w.window_blocks - 1
+    q, k, v = S.gen_layer(w, 0, cur)
+    ctx = hc.Context(hc.config_from_workload(w), 0)
+    ctx.set_head_types(0, types, cur, dev_bf16(k), dev_bf16(v))
+    o = out_tensor(w)
+    ctx.attention(0, dev_bf16(q), types, o)
+    torch.cuda.synchronize()
+    ref = O.routed_attention(types, q, k, v, w.grid_h, w.grid_w, w.frames_per_block,
+                             w.spatial_radius)
+    assert_close(o.cpu().numpy(), ref, f"balanced tail, 64-dim, types={types.tolist()}")
