@@ -248,12 +248,13 @@ hc_status hc_attention(hc_ctx *ctx, int layer, const void *q, const uint8_t *hea
  * the host and does not synchronise: the layer's work list, the per-block
  * partial results of Global (and two-block Sink/Dummy) heads and the split
  * partials of Spatial heads live in one fixed array of HC_STATIC_SCRATCH_BYTES
- * per GPU, held by the library until the process ends; the work list is
+ * per GPU, held by the library until the process ends (Spatial and other
+ * partials take turns in the same place where not both fit); the work list is
  * written by a kernel on `stream` at every call.  Every call on a GPU uses
  * that GPU's array and leaves its contents behind, so calls that overlap on
  * one GPU (other streams, other contexts, other threads) race and must be
  * ordered by the caller.  A layer whose work needs more than the array holds
- * (the Spatial split is dropped first) is HC_E_INVAL with the size in
+ * (the Spatial split is reduced to what fits first) is HC_E_INVAL with the size in
  * hc_last_error, before anything is enqueued; so is a context with the cell
  * variant (spatial_cell > 0).  The layer's buffers are the context's, set up
  * beforehand by hc_set_head_types / hc_classify_heads. */

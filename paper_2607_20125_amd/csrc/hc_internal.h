@@ -1,5 +1,5 @@
 // Internal structures shared by the host runtime (hc_runtime.cpp) and the
-// gfx950 kernels (hc_dense.hip, hc_spatial.hip, hc_cache.hip).  Not part of the public ABI.
+// gfx950 kernels (hc_dense.hip, hc_spatial.hip, hc_merge.hip, hc_cache.hip).  Not part of the public ABI.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -52,7 +52,7 @@ struct SpatialArgs {
   // The key frames of the window may be split into n_split contiguous ranges,
   // one work group each; the groups then write unnormalised partial results
   // (part: [n_split][n_sp][L][d], part_ml: [n_split][n_sp][L] {max (log2), sum})
-  // that spatial_merge_kernel combines into o.  n_split = 1 writes o directly.
+  // that launch_merge combines into o.  n_split = 1 writes o directly.
   int32_t n_split;
   float *part;
   float *part_ml;
@@ -116,11 +116,12 @@ struct ClsReduceArgs {
 // Only separates kernel symbols (and so profiler statistics) by caller; the code is the same.
 enum class DenseRole { kRouted, kFullWindow, kClassify, kVariant, kSinkDummyOnly };
 hipError_t launch_dense(const DenseArgs &a, int head_dim, DenseRole role, hipStream_t s);
-hipError_t launch_combine(const CombineArgs &a, hipStream_t s);
-// Spatial kernel, followed by the merge of the partial results when a.n_split > 1.
 // The role only separates kernel symbols by caller, as for the dense kernel.
 enum class SpatialRole { kRouted, kClassify, kSpatialOnly };
 hipError_t launch_spatial(const SpatialArgs &a, int head_dim, SpatialRole role, hipStream_t s);
+// The merge of the dense items (c.n_items may be 0) and of the Spatial splits (none
+// unless s.n_split > 1) in one launch.
+hipError_t launch_merge(const CombineArgs &c, const SpatialArgs &s, int head_dim, hipStream_t st);
 hipError_t launch_scatter(ScatterArgs a, int n_heads, hipStream_t s);   // sets n_tiles
 hipError_t launch_stats(const StatsArgs &a, hipStream_t s);
 hipError_t launch_cls_reduce(const ClsReduceArgs &a, hipStream_t s);

@@ -80,13 +80,28 @@ struct HeadKV {
 struct DensePlanShape {
   int L = 0;                 // tokens per block
   int nv = 0;                // valid window blocks
+  int g_parts = 0;           // key ranges per Global head (0: one per window block)
   int sd_blocks = 1;         // Sink-Dummy slots per head (1 or 2)
   int F = 1, grid_h = 0, grid_w = 0, cell = 0;   // cell variant (cell > 0)
   const CellTables *cells = nullptr;
 };
 
+// Keys [*kv0, *kv1) of part p of a Global head's nv L keys: window block p when
+// there are as many parts as blocks (or parts is 0), else equal runs of tiles.
+inline HC_HD void global_part(int L, int nv, int parts, int p, int32_t *kv0, int32_t *kv1) {
+  if (parts == 0 || parts == nv) {
+    *kv0 = p * L;
+    *kv1 = *kv0 + L;
+    return;
+  }
+  const int64_t keys = (int64_t)nv * L, tiles = (keys + kKTile - 1) / kKTile;
+  const int64_t end = kKTile * (tiles * (p + 1) / parts);
+  *kv0 = (int32_t)(kKTile * (tiles * p / parts));
+  *kv1 = (int32_t)(end < keys ? end : keys);
+}
+
 // Dense work of one routed layer: Global heads get one unit per window block
-// and 128-query tile (partials merged per tile), Sink/Dummy heads one unit per
+// (or other part of the window) and 128-query tile (partials merged per tile), Sink/Dummy heads one unit per
 // tile over their block (per block slot in the two-block variant once a second
 // block exists, merged like a Global head), cells one query-mapped unit per
 // 128 queries of a cell.  Units are ordered (head, key block, query tile) so
@@ -103,20 +118,21 @@ inline void plan_dense_units(const DensePlanShape &s, const std::vector<HeadKV> 
   const int nqt = (L + kQTile - 1) / kQTile;
   units.clear();
   comb.clear();
+  const int gp = s.g_parts > 0 ? s.g_parts : nv;
   int slot = 0;
   for (const HeadKV &h : global) {
-    for (int blk = 0; blk < nv; ++blk)
+    for (int part = 0; part < gp; ++part)
       for (int qt = 0; qt < nqt; ++qt) {
         DenseUnit u{};
         u.k = h.k; u.v = h.v; u.head = h.head; u.q0 = qt * kQTile;
-        u.kv0 = blk * L; u.kv1 = (blk + 1) * L;
-        u.slot = nv > 1 ? slot + qt * nv + blk : -1;
+        global_part(L, nv, gp, part, &u.kv0, &u.kv1);
+        u.slot = gp > 1 ? slot + qt * gp + part : -1;
         units.push_back(u);
       }
-    if (nv > 1) {
+    if (gp > 1) {
       for (int qt = 0; qt < nqt; ++qt)
-        comb.push_back(CombineItem{h.head, qt * kQTile, slot + qt * nv, nv, 0, 0});
-      slot += nqt * nv;
+        comb.push_back(CombineItem{h.head, qt * kQTile, slot + qt * gp, gp, 0, 0});
+      slot += nqt * gp;
     }
   }
   const int sd_parts = (s.sd_blocks == 2 && nv >= 2) ? 2 : 1;
@@ -167,30 +183,34 @@ struct StaticPlan {
   const uint16_t *k_g, *v_g, *k_sd, *v_sd;   // buffer bases; head slot s at s * keys * d
   int64_t g_keys, sd_keys;
   int32_t d, L, nv, nqt, sd_parts, n_g, n_sd;
+  int32_t g_parts;                           // key ranges per Global head (0: one per block)
   int8_t g_head[64], sd_head[64];            // head id of each buffer slot
 };
 
+inline HC_HD int static_g_parts(const StaticPlan &p) { return p.g_parts > 0 ? p.g_parts : p.nv; }
 inline HC_HD int static_n_units(const StaticPlan &p) {
-  return (p.n_g * p.nv + p.n_sd * p.sd_parts) * p.nqt;
+  return (p.n_g * static_g_parts(p) + p.n_sd * p.sd_parts) * p.nqt;
 }
 inline HC_HD int static_n_comb(const StaticPlan &p) {
-  return ((p.nv > 1 ? p.n_g : 0) + (p.sd_parts > 1 ? p.n_sd : 0)) * p.nqt;
+  return ((static_g_parts(p) > 1 ? p.n_g : 0) + (p.sd_parts > 1 ? p.n_sd : 0)) * p.nqt;
 }
 inline HC_HD int static_n_slots(const StaticPlan &p) {
-  return ((p.nv > 1 ? p.n_g * p.nv : 0) + (p.sd_parts > 1 ? p.n_sd * p.sd_parts : 0)) * p.nqt;
+  const int gp = static_g_parts(p);
+  return ((gp > 1 ? p.n_g * gp : 0) + (p.sd_parts > 1 ? p.n_sd * p.sd_parts : 0)) * p.nqt;
 }
 
 inline HC_HD DenseUnit static_dense_unit(const StaticPlan &p, int i) {
   DenseUnit u{};
-  const int ng_units = p.n_g * p.nv * p.nqt;
-  const int g_slots = p.nv > 1 ? ng_units : 0;
-  if (i < ng_units) {                         // Global: (head, block, query tile)
-    const int qt = i % p.nqt, blk = (i / p.nqt) % p.nv, gi = i / (p.nqt * p.nv);
+  const int gp = static_g_parts(p);
+  const int ng_units = p.n_g * gp * p.nqt;
+  const int g_slots = gp > 1 ? ng_units : 0;
+  if (i < ng_units) {                         // Global: (head, part, query tile)
+    const int qt = i % p.nqt, part = (i / p.nqt) % gp, gi = i / (p.nqt * gp);
     u.k = p.k_g + (int64_t)gi * p.g_keys * p.d;
     u.v = p.v_g + (int64_t)gi * p.g_keys * p.d;
     u.head = p.g_head[gi];
-    u.kv0 = blk * p.L;
-    u.slot = p.nv > 1 ? gi * p.nqt * p.nv + qt * p.nv + blk : -1;
+    global_part(p.L, p.nv, gp, part, &u.kv0, &u.kv1);
+    u.slot = gp > 1 ? gi * p.nqt * gp + qt * gp + part : -1;
     u.q0 = qt * kQTile;
   } else {                                    // Sink/Dummy: (head, block slot, query tile)
     const int j = i - ng_units;
@@ -199,23 +219,24 @@ inline HC_HD DenseUnit static_dense_unit(const StaticPlan &p, int i) {
     u.v = p.v_sd + (int64_t)si * p.sd_keys * p.d;
     u.head = p.sd_head[si];
     u.kv0 = part * p.L;
+    u.kv1 = u.kv0 + p.L;
     u.slot = p.sd_parts > 1 ? g_slots + si * p.nqt * p.sd_parts + qt * p.sd_parts + part : -1;
     u.q0 = qt * kQTile;
   }
-  u.kv1 = u.kv0 + p.L;
   return u;
 }
 
 inline HC_HD CombineItem static_comb_item(const StaticPlan &p, int i) {
-  const int ng_items = p.nv > 1 ? p.n_g * p.nqt : 0;
-  const int g_slots = p.nv > 1 ? p.n_g * p.nv * p.nqt : 0;
+  const int gp = static_g_parts(p);
+  const int ng_items = gp > 1 ? p.n_g * p.nqt : 0;
+  const int g_slots = gp > 1 ? p.n_g * gp * p.nqt : 0;
   CombineItem it{};
   if (i < ng_items) {
     const int qt = i % p.nqt, gi = i / p.nqt;
     it.head = p.g_head[gi];
     it.q0 = qt * kQTile;
-    it.slot0 = gi * p.nqt * p.nv + qt * p.nv;
-    it.n_slots = p.nv;
+    it.slot0 = gi * p.nqt * gp + qt * gp;
+    it.n_slots = gp;
   } else {
     const int j = i - ng_items;
     const int qt = j % p.nqt, si = j / p.nqt;
@@ -225,6 +246,17 @@ inline HC_HD CombineItem static_comb_item(const StaticPlan &p, int i) {
     it.n_slots = p.sd_parts;
   }
   return it;
+}
+
+// Key ranges per Global head: one for windows of at most 12 key tiles (24 with
+// 64-dim heads), else one per window block.  Up to there the merge launch of the
+// ranges' partials takes longer than the tiles it saves: append and attention of
+// six Global and six Sink/Dummy heads, one range against one per block, take 19.5
+// against 22.0 us at 8 tiles, 20.0 against 22.0 at 12 and 23.6 against 22.4 at 16;
+// 64-dim heads 19.5 against 22.4 at 16 and 22.4 both at 32.  (Not asked where the
+// layer's Spatial heads need the merge launch anyway.)
+inline int global_parts(int d, int L, int nv) {
+  return ((int64_t)nv * L + kKTile - 1) / kKTile <= (d == 64 ? 24 : 12) ? 1 : nv;
 }
 
 // The classification sweep (Sec. 4.2): per head one unit per window block and
@@ -501,6 +533,50 @@ inline void balance_units(int n_cu, std::vector<DenseUnit> &units, std::vector<C
     none.head = -1;
     for (size_t i = runs[x].size(); i < longest; ++i) units.push_back(none);
   }
+}
+
+// Key ranges per Global head of a work list that is not tail-balanced (the
+// device-built one): the number whose runs end first, counting the merge of its
+// partial slots, with at most max_slots slots.  One range per window block may
+// leave the last round of a run nearly empty (480P, three Global and seven
+// Sink/Dummy heads: 1036 units on 512 slots, three rounds of 73 tiles; six ranges
+// give 925 units of at most 86 tiles in two).  One range per block stays unless
+// another number ends at least 2% earlier.
+inline int static_global_parts(StaticPlan p, int n_cu, int groups_per_cu, int64_t max_slots,
+                               bool merged_anyway) {
+  using namespace plan_detail;
+  const int small = merged_anyway ? p.nv : global_parts(p.d, p.L, p.nv);
+  if (p.n_g == 0 || n_cu <= 0 || n_cu % 8 != 0 || small < p.nv) return small;
+  // in key tiles of a full launch (1.8 us each): a merge launch, and 66 KB a
+  // slot written and read at 4 TB/s
+  constexpr double kMergeTiles = 2.5, kSlotTiles = 0.018;
+  const int slots = groups_per_cu * n_cu / 8;
+  double best = 0;
+  int best_parts = p.nv;
+  auto end_of = [&](int parts, double most) {   // not counted further than `most`
+    p.g_parts = parts;
+    const int n = static_n_units(p), per = n / 8, rem = n % 8;
+    double end = 0;
+    for (int x = 0; x < 8; ++x) {
+      const int b = x * per + std::min(x, rem), e = b + per + (x < rem ? 1 : 0);
+      SlotClock clock(slots);
+      for (int i = b; i < e && clock.end < most; ++i)
+        clock.add(unit_tiles(static_dense_unit(p, i)) + kUnitOverheadTiles);
+      end = std::max(end, clock.end);
+      if (end >= most) break;
+    }
+    const int ns = static_n_slots(p);
+    return end + (ns > 0 ? kMergeTiles + kSlotTiles * ns : 0.0);
+  };
+  best = end_of(p.nv, 1e30);
+  const int64_t tiles = ((int64_t)p.nv * p.L + kKTile - 1) / kKTile;
+  for (int parts = 1; parts <= std::min<int64_t>(kMaxSrcBlocks, tiles); ++parts) {
+    p.g_parts = parts;
+    if (parts == p.nv || static_n_slots(p) > max_slots) continue;
+    const double t = end_of(parts, best);
+    if (t < best * 0.98) { best = t; best_parts = parts; }
+  }
+  return best_parts;
 }
 
 }  // namespace hc

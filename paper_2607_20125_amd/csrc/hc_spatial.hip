@@ -3,8 +3,6 @@
 // proxy; the deployed Spatial path of this library).
 #include "hc_device.h"
 
-#include <algorithm>
-
 namespace hc {
 namespace {
 using namespace dev;
@@ -433,35 +431,6 @@ __global__ __launch_bounds__(64 * F, (F >= 3 ? 3 : F)) void attn_spatial_kernel(
   }
 }
 
-// ---------------------------------------------------------------------------
-// Merge of the per-split partial results of the Spatial heads: for each
-// (head, query) O = sum_s 2^(m_s - M) O_s / sum_s 2^(m_s - M) l_s, M = max_s m_s.
-// One thread per 4 output dims.
-// ---------------------------------------------------------------------------
-__global__ __launch_bounds__(256) void spatial_merge_kernel(SpatialArgs a, int D) {
-  const int nq = D / 4;
-  const int64_t total = (int64_t)a.n_sp * a.L * nq;
-  const int64_t plane = (int64_t)a.n_sp * a.L;        // rows per split
-  for (int64_t e = (int64_t)blockIdx.x * 256 + threadIdx.x; e < total;
-       e += (int64_t)gridDim.x * 256) {
-    const int64_t row = e / nq;                          // hs * L + token
-    const int c4 = (int)(e % nq);
-    float M = kMInit;
-    for (int sp = 0; sp < a.n_split; ++sp) M = fmaxf(M, a.part_ml[2 * (sp * plane + row)]);
-    f32x4 sum = {0.f, 0.f, 0.f, 0.f};
-    float den = 0.f;
-    for (int sp = 0; sp < a.n_split; ++sp) {
-      const int64_t rs = sp * plane + row;
-      const float w = __builtin_amdgcn_exp2f(a.part_ml[2 * rs] - M);
-      den += w * a.part_ml[2 * rs + 1];
-      sum += w * *reinterpret_cast<const f32x4 *>(a.part + rs * D + 4 * c4);
-    }
-    const int hs = (int)(row / a.L), tok = (int)(row % a.L);
-    const float inv = den > 0.f ? 1.f / den : 0.f;
-    *reinterpret_cast<f32x4 *>(a.o + ((size_t)a.heads[hs] * a.L + tok) * D + 4 * c4) = sum * inv;
-  }
-}
-
 template <int D, int F, int R>
 hipError_t launch_spatial_f(const SpatialArgs &a, dim3 grid, hipStream_t s) {
   const int G = spatial_groups(a.r);
@@ -497,13 +466,8 @@ hipError_t launch_spatial(const SpatialArgs &a, int head_dim, SpatialRole role, 
   if (a.F < 1 || a.F > 4 || a.n_split < 1 || (a.n_split > 1 && (!a.part || !a.part_ml)))
     return hipErrorInvalidValue;
   dim3 grid((unsigned)nblk);
-  hipError_t e = head_dim == 128 ? launch_spatial_r<128>(a, grid, role, s)
-                                 : launch_spatial_r<64>(a, grid, role, s);
-  if (e != hipSuccess || a.n_split == 1) return e;
-  const int64_t threads = (int64_t)a.n_sp * a.L * (head_dim / 4);
-  const unsigned blocks = (unsigned)std::min<int64_t>((threads + 255) / 256, 8192);
-  hipLaunchKernelGGL(spatial_merge_kernel, dim3(blocks), dim3(256), 0, s, a, head_dim);
-  return hipGetLastError();
+  return head_dim == 128 ? launch_spatial_r<128>(a, grid, role, s)
+                         : launch_spatial_r<64>(a, grid, role, s);
 }
 
 }  // namespace hc

@@ -242,7 +242,7 @@ static void cell_regions(int Hg, int Wg, int F, int W, int cs, int n_cu) {
 // item index) equals plan_dense_units' list before balancing, unit by unit.
 static int n_static_plans = 0;
 
-static void static_plan_matches(int L, int nv, int sd_blocks, int n_g, int n_sd) {
+static void static_plan_matches(int L, int nv, int sd_blocks, int n_g, int n_sd, int g_parts = 0) {
   ++n_static_plans;
   const int D = 64, W = 7;
   const int64_t gk = global_buffer_keys(W, L), sk = sd_buffer_keys(sd_blocks, L);
@@ -250,7 +250,7 @@ static void static_plan_matches(int L, int nv, int sd_blocks, int n_g, int n_sd)
   p.k_g = fake_base(0, 0); p.v_g = fake_base(1, 0); p.k_sd = fake_base(2, 0); p.v_sd = fake_base(3, 0);
   p.g_keys = gk; p.sd_keys = sk; p.d = D; p.L = L; p.nv = nv; p.nqt = (L + kQTile - 1) / kQTile;
   p.sd_parts = (sd_blocks == 2 && nv >= 2) ? 2 : 1;
-  p.n_g = n_g; p.n_sd = n_sd;
+  p.n_g = n_g; p.n_sd = n_sd; p.g_parts = g_parts;
   std::vector<HeadKV> g, sd;
   // heads interleaved as a table would put them: buffer slot order = head order
   int head = 0;
@@ -264,7 +264,7 @@ static void static_plan_matches(int L, int nv, int sd_blocks, int n_g, int n_sd)
     sd.push_back(HeadKV{h, fake_base(2, i * sk * D), fake_base(3, i * sk * D)});
   }
   DensePlanShape shape;
-  shape.L = L; shape.nv = nv; shape.sd_blocks = sd_blocks;
+  shape.L = L; shape.nv = nv; shape.sd_blocks = sd_blocks; shape.g_parts = g_parts;
   std::vector<DenseUnit> units;
   std::vector<CombineItem> comb;
   plan_dense_units(shape, g, sd, {}, 0, units, comb);
@@ -294,6 +294,23 @@ int main() {
       for (int sdb = 1; sdb <= 2; ++sdb)
         for (auto gs : std::vector<std::pair<int, int>>{{0, 0}, {1, 0}, {0, 3}, {3, 2}, {12, 0}, {0, 12}})
           static_plan_matches(L, nv, sdb, gs.first, gs.second);
+  // ... and with the window in other ranges than its blocks: whole tiles, each
+  // key in exactly one, none empty
+  for (int L : {8, 72, 128, 384, 4680})
+    for (int nv = 1; nv <= 7; ++nv) {
+      const int tiles = (nv * L + kKTile - 1) / kKTile;
+      for (int parts = 1; parts <= std::min(tiles, kMaxSrcBlocks); ++parts) {
+        static_plan_matches(L, nv, 1, 3, 2, parts);
+        int end = 0;
+        for (int i = 0; i < parts; ++i) {
+          int32_t a, b;
+          global_part(L, nv, parts, i, &a, &b);
+          CHECK(a == end && b > a && (parts == nv || a % kKTile == 0), "part %d of %d: [%d, %d)", i, parts, a, b);
+          end = b;
+        }
+        CHECK(end == nv * L, "parts end at %d of %d", end, nv * L);
+      }
+    }
   std::printf("plan_check: %d device-built work lists match the host planner\n", n_static_plans);
   // key ranges: every L that is a multiple of 8 up to 4096, every W from 2 to 32
   for (int L = 8; L <= 4096; L += 8)

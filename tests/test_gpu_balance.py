@@ -51,3 +51,44 @@ def test_balanced_tail_64_dim_heads(hc, types):
     ref = O.routed_attention(types, q, k, v, w.grid_h, w.grid_w, w.frames_per_block,
                              w.spatial_radius)
     assert_close(o.cpu().numpy(), ref, f"balanced tail, 64-dim, types={types.tolist()}")
+
+
+@pytest.mark.parametrize("d, L, nv", [(128, 128, 6), (128, 136, 6), (64, 256, 6), (64, 264, 6),
+                                      (128, 8, 1)])
+def test_uncut_small_windows(hc, d, L, nv):
+    """Windows of up to 12 key tiles (24 with 64-dim heads) are one unit per query tile
+    that writes its output itself; one tile more goes back to one unit per block."""
+    import torch
+    types = np.array([3, 0, 1, 3], np.uint8)
+    w = S.Workload("uncut", 1, 4, d, 8, L // 8, 1, 7, 1, 1, 483, (1, 1, 0, 2))
+    cur = nv - 1
+    q, k, v = S.gen_layer(w, 0, cur)
+    ctx = hc.Context(hc.config_from_workload(w), 0)
+    ctx.set_head_types(0, types, cur, dev_bf16(k), dev_bf16(v))
+    ref = O.routed_attention(types, q, k, v, w.grid_h, w.grid_w, w.frames_per_block,
+                             w.spatial_radius)
+    for call in ("attention", "attention_static"):
+        o = out_tensor(w)
+        getattr(ctx, call)(0, dev_bf16(q), types, o)
+        torch.cuda.synchronize()
+        assert_close(o.cpu().numpy(), ref, f"{call} d={d} L={L} nv={nv}")
+
+
+@pytest.mark.parametrize("types", [(3, 3, 3, 0, 0, 1, 1, 0, 1, 1, 2, 2), (3, 3, 1, 2), (3, 0)])
+def test_static_key_ranges_480p(hc, types):
+    """The no-allocation call cuts Global windows into as many ranges as end first, not
+    at block borders, and its Spatial partials reuse the merged dense partials' place."""
+    import torch
+    types = np.array(types, np.uint8)
+    w = S.Workload("ranges", 1, len(types), 128, 30, 52, 3, 7, 4, 2, 484, (0, 0, 0, len(types)))
+    ctx = hc.Context(hc.config_from_workload(w), 0)
+    dev = torch.device("cuda:0")
+    shape = (w.n_heads, w.window_tokens, w.head_dim)
+    ctx.set_head_types(0, types, w.window_blocks - 1, S.device_normal_bf16(shape, 1, dev),
+                       S.device_normal_bf16(shape, 2, dev))
+    q = S.device_normal_bf16((w.n_heads, w.block_tokens, w.head_dim), 3, dev)
+    ref, got = out_tensor(w), out_tensor(w)
+    ctx.attention(0, q, types, ref)
+    ctx.attention_static(0, q, types, got)
+    torch.cuda.synchronize()
+    assert_close(got.cpu().numpy(), ref.cpu().numpy().astype(np.float64), f"ranges {types.tolist()}")
