@@ -12,7 +12,7 @@ PKG = os.path.dirname(os.path.abspath(__file__))
 ROOT = os.path.dirname(PKG)
 CSRC = os.path.join(PKG, "csrc")
 LIB = os.path.join(PKG, "libheadcast.so")
-SOURCES = ["hc_runtime.cpp", "hc_dense.hip", "hc_spatial.hip", "hc_merge.hip", "hc_cache.hip", "hc_static.hip"]
+SOURCES = ["hc_runtime.cpp", "hc_dense.hip", "hc_dense128.hip", "hc_spatial.hip", "hc_merge.hip", "hc_cache.hip", "hc_static.hip"]
 
 
 def hipcc() -> str:
@@ -29,11 +29,12 @@ def build_library(verbose: bool = False) -> str:
     flags = ["--offload-arch=gfx950", "-O3", "-std=c++17", "-fPIC",
              # keep the compiler from forming packed fp32 instructions
              "-Xclang", "-target-feature", "-Xclang", "-packed-fp32-ops",
-             # MFMA results in vector registers (the online-softmax rescale works on them)
-             "-mllvm", "-amdgpu-mfma-vgpr-form",
              # no NaN is produced on these paths: max needs no NaN canonicalisation
              "-fno-honor-nans",
              "-I" + os.path.join(ROOT, "include"), "-I" + CSRC]
+    # MFMA results in vector registers (the online-softmax rescale works on them), except
+    # where the accumulators of 64 queries per wave need the other half of the register file
+    vgpr_form = ["-mllvm", "-amdgpu-mfma-vgpr-form"]
     tmp = LIB + ".tmp"
 
     def run(cmd):
@@ -48,8 +49,8 @@ def build_library(verbose: bool = False) -> str:
 
     with tempfile.TemporaryDirectory(prefix="headcast_build_") as tdir:
         objs = [os.path.join(tdir, src + ".o") for src in SOURCES]
-        cmds = [[hipcc()] + flags + ["-c", os.path.join(CSRC, src), "-o", obj]
-                for src, obj in zip(SOURCES, objs)]
+        cmds = [[hipcc()] + flags + ([] if src == "hc_dense128.hip" else vgpr_form)
+                + ["-c", os.path.join(CSRC, src), "-o", obj] for src, obj in zip(SOURCES, objs)]
         with concurrent.futures.ThreadPoolExecutor(max_workers=len(cmds)) as ex:
             list(ex.map(run, cmds))
         run([hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC"] + objs + ["-o", tmp])

@@ -1,5 +1,6 @@
-// Dense softmax attention of 128-query tiles over a contiguous key range.
-// Global path (the whole window), Sink/Dummy paths (one block) and the
+// Dense softmax attention of 128-query tiles over a contiguous key range, on
+// waves of 32 queries (64-dim heads, and launches of 128-dim heads that are too
+// short for hc_dense128.hip), and the launcher of both kernels.  Global path (the whole window), Sink/Dummy paths (one block) and the
 // classification proxies O_ref, O_sink, O_dummy (Sec. 4.4, Eq. 2).
 #include "hc_device.h"
 
@@ -10,8 +11,9 @@ using namespace dev;
 // ---------------------------------------------------------------------------
 // Dense kernel: one work group = kQTile (128) queries of one unit on 4 waves of
 // 32 queries; two work groups share a CU (two waves per SIMD, 2 x 80 KB of LDS;
-// three with 64-dim heads), so one group's barrier waits and softmax overlap the
-// others' matrix work.
+// three with 64-dim heads, 40 KB and 168 registers each), so one group's barrier
+// waits and softmax overlap the others' matrix work.  With 64-dim heads a tile has
+// half the products for the same softmax, and the third wave per SIMD overlaps them.
 // K/V tiles of 64 keys are fetched kDist tiles ahead of use (K ring of kDist,
 // V ring of kDist + 1 buffers); one barrier per tile.
 // The key loop is software-pipelined inside each wave: while the matrix cores
@@ -264,19 +266,17 @@ __global__ __launch_bounds__(64 * kDenseWaves, dense_groups_per_cu(D)) void attn
       pv(fo, vb, pf);
       if constexpr (!FO) mx = rowmax(nxt);
       if constexpr (FO) {
-        // Instruction order of the fixed-offset step: the 16 matrix
-        // instructions of S(t+1) with one vector instruction of the softmax
-        // of tile t each, each K operand read one MFMA ahead; then the 16 PV(t)
-        // and 4 row-sum matrix instructions with the V reads and up to three
-        // vector instructions each, so the rest of the softmax runs beside the
-        // products of the 16-key chunks whose probabilities are done.  Measured
-        // against five per S(t+1) product and none after: 2-4% faster; none
-        // during S(t+1) was slower, as was leaving the order to the scheduler.
-        // With 64-dim heads a tile has half the products for the same softmax:
-        // three vector instructions per S(t+1) product (8 of them), up to five
-        // per PV and row-sum product (12).  Together with the third work group
-        // per CU 505 -> 463 us for 16 full-window heads of 25392 keys (476 us
-        // with two groups; 466 with three and the compiler's order).
+        // Instruction order of the fixed-offset step: the matrix instructions of
+        // S(t+1) with kSV vector instructions of the softmax of tile t each, each K
+        // operand read one MFMA ahead; then the PV(t) and row-sum matrix
+        // instructions with the V reads and up to kPV vector instructions each, so
+        // the rest of the softmax runs beside the products of the 16-key chunks
+        // whose probabilities are done.  128-dim heads: one and three, 2-4% faster
+        // than five and none; none during S(t+1) was slower, as was leaving the
+        // order to the scheduler.  With 64-dim heads a tile has half the products
+        // for the same softmax: three and five; together with the third work group
+        // per CU 505 -> 463 us for 16 full-window heads of 25392 keys (476 us with
+        // two groups; 466 with three and the compiler's order).
         constexpr int kSV = D == 64 ? 3 : 1, kPV = D == 64 ? 5 : 3;
         __builtin_amdgcn_sched_group_barrier(0x100, 2, 0);     // DS reads
 #pragma unroll
@@ -412,6 +412,7 @@ __global__ __launch_bounds__(64 * kDenseWaves, dense_groups_per_cu(D)) void attn
 
 hipError_t launch_dense(const DenseArgs &a, int head_dim, DenseRole role, hipStream_t s) {
   if (a.n_units <= 0) return hipSuccess;
+  if (head_dim == 128 && a.wide_waves) return launch_dense128(a, role, s);
   dim3 grid(a.n_units), block(64 * kDenseWaves);
 #define HC_DENSE(DD, RR) hipLaunchKernelGGL((attn_dense_kernel<DD, RR>), grid, block, 0, s, a)
   if (head_dim == 128) {

@@ -1,5 +1,5 @@
 // Internal structures shared by the host runtime (hc_runtime.cpp) and the
-// gfx950 kernels (hc_dense.hip, hc_spatial.hip, hc_merge.hip, hc_cache.hip).  Not part of the public ABI.
+// gfx950 kernels (hc_dense.hip, hc_dense128.hip, hc_spatial.hip, hc_merge.hip, hc_cache.hip).  Not part of the public ABI.
 #pragma once
 
 #include <hip/hip_runtime.h>
@@ -22,6 +22,7 @@ struct DenseArgs {
   int32_t n_units;
   int32_t L;
   float scale_log2;        // softmax scale * log2(e)
+  bool wide_waves;         // 128-dim heads: 64 queries per wave (dense_wide_waves)
 };
 
 struct CombineArgs {
@@ -116,6 +117,7 @@ struct ClsReduceArgs {
 // Only separates kernel symbols (and so profiler statistics) by caller; the code is the same.
 enum class DenseRole { kRouted, kFullWindow, kClassify, kVariant, kSinkDummyOnly };
 hipError_t launch_dense(const DenseArgs &a, int head_dim, DenseRole role, hipStream_t s);
+hipError_t launch_dense128(const DenseArgs &a, DenseRole role, hipStream_t s);   // its 128-dim heads
 // The role only separates kernel symbols by caller, as for the dense kernel.
 enum class SpatialRole { kRouted, kClassify, kSpatialOnly };
 hipError_t launch_spatial(const SpatialArgs &a, int head_dim, SpatialRole role, hipStream_t s);

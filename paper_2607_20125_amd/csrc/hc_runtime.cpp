@@ -40,6 +40,7 @@ struct Layer {
   const DenseUnit *units = nullptr;
   const CombineItem *comb = nullptr;
   int n_units = 0, n_comb = 0;
+  int64_t plan_tiles = 0;      // key tiles of all units
   int plan_nv = -1;            // valid window blocks the plan was built for
   bool plan_used = false;      // launches may still read the plan's memory
   int static_nv = -1;          // window fill that static_parts was chosen for
@@ -389,6 +390,8 @@ hc_status ensure_plan(hc_ctx *c, Layer &l, int nv) {
   l.comb = (const CombineItem *)((const unsigned char *)l.plan.p + b_units);
   l.n_units = (int)units.size();
   l.n_comb = (int)comb.size();
+  l.plan_tiles = 0;
+  for (const DenseUnit &u : units) l.plan_tiles += plan_detail::unit_tiles(u);
   l.plan_nv = nv;
   l.plan_used = true;
   return HC_OK;
@@ -492,6 +495,7 @@ hc_status check_attention(hc_ctx *c, int layer, const void *q, const uint8_t *he
 struct LayerWork {
   const DenseUnit *units = nullptr;
   int n_units = 0;
+  int64_t tiles = 0;           // key tiles of all units
   const CombineItem *comb = nullptr;
   int n_comb = 0;
   float *part = nullptr;
@@ -563,6 +567,7 @@ hc_status run_layer(hc_ctx *c, const Layer &l, int nv, const void *q, float *o,
     a.n_units = wk.n_units;
     a.L = c->L;
     a.scale_log2 = c->scale * 1.4426950408889634f;
+    a.wide_waves = dense_wide_waves(wk.tiles, c->n_cu);
     const DenseRole role = (int)l.g_heads.size() == H ? DenseRole::kFullWindow
                            : (c->cfg.spatial_cell > 0 || c->cfg.sd_blocks == 2)
                                ? DenseRole::kVariant
@@ -783,6 +788,7 @@ hc_status hc_attention(hc_ctx *c, int layer, const void *q, const uint8_t *head_
   LayerWork wk;
   wk.units = l.units;
   wk.n_units = l.n_units;
+  wk.tiles = l.plan_tiles;
   wk.comb = l.comb;
   wk.n_comb = l.n_comb;
   wk.part = (float *)c->part.p;
@@ -854,6 +860,8 @@ hc_status hc_attention_static(hc_ctx *c, int layer, const void *q, const uint8_t
   LayerWork wk;
   wk.units = (const DenseUnit *)base;
   wk.n_units = (int)n_units;
+  wk.tiles = (p.n_g * (round_up_tiles((int64_t)nv * c->L) / kKTile) +
+              (int64_t)p.n_sd * p.sd_parts * (round_up_tiles(c->L) / kKTile)) * p.nqt;
   wk.comb = (const CombineItem *)(base + b_units);
   wk.n_comb = (int)n_comb;
   wk.part = (float *)(base + b_lists);
@@ -990,6 +998,7 @@ hc_status hc_classify_heads(hc_ctx *c, int layer, int64_t cur_block, const void 
     a.n_units = c->cls_n_units;
     a.L = L;
     a.scale_log2 = c->scale * 1.4426950408889634f;
+    a.wide_waves = dense_wide_waves(c->cls_n_units * (round_up_tiles(L) / kKTile), c->n_cu);
     st = timed_launch(c, s, HC_K_DENSE,
                       [&] { return launch_dense(a, D, DenseRole::kClassify, s); });
     if (st != HC_OK) return st;

@@ -133,3 +133,40 @@ def test_many_overflowed_probabilities_per_row(hc, types):
     ref = O.routed_attention(types, q, k, v, w.grid_h, w.grid_w, w.frames_per_block,
                              w.spatial_radius)
     assert_close(o.cpu().numpy(), ref, f"overflowed rows types={types.tolist()}")
+
+
+@pytest.mark.parametrize("L, where", [
+    (2056, "none"), (2112, "none"), (2176, "none"), (2184, "none"),   # 33, 33, 34, 35 tiles
+    (2056, "all"),     # the row sums of the first tiles end the fixed-offset pass
+    (2056, "late"),    # only late keys overflow: the pass runs to its end first
+    (2056, "one"),     # one query overflows: both waves of its work group change over
+    (1984, "all"),     # 31 tiles: no look at the first tiles
+    (1984, "none")])
+def test_wide_wave_units_and_early_fallback(hc, L, where):
+    """Launches of 128-dim heads with enough tiles for waves of 64 queries (64 Global heads
+    of three blocks): tile counts of every remainder of its two-step loop, ragged and
+    full last tiles and query tiles, and both sides of the early row-sum check."""
+    import torch
+    H, W = 64, 3
+    w = S.Workload("wide", 1, H, 128, 8, L // 8, 1, W, 1, 1, 77, (0, 0, 0, H))
+    dev = torch.device("cuda:0")
+    q, k, v = (S.device_normal_bf16((H, n * L, 128), 5 + i, dev) for i, n in enumerate((1, W, W)))
+    if where == "all":
+        q *= 40
+    elif where == "one":
+        q[:, 5] *= 40
+    elif where == "late":
+        for blk in range(W):
+            k[:, (blk + 1) * L - 3] *= 40
+    types = np.full(H, S.GLOBAL, np.uint8)
+    ctx = hc.Context(hc.config_from_workload(w), 0)
+    ctx.set_head_types(0, types, W - 1, k, v)
+    o = out_tensor(w)
+    ctx.attention(0, q, types, o)
+    torch.cuda.synchronize()
+    heads = [0, 41, 63]
+    bits = lambda t: t[heads].view(torch.int16).cpu().numpy().view(np.uint16)
+    ref = O.routed_attention(types[heads], bits(q), bits(k), bits(v), w.grid_h, w.grid_w, 1, 1)
+    assert_close(o[heads].cpu().numpy(), ref, f"L={L} {where}")
+    assert bool(o.isfinite().all())
+    ctx.close()
