@@ -37,7 +37,8 @@ CSRC = os.path.join(ROOT, "paper_2607_20125_amd", "csrc")
 # sources that determine each kernel's code: a counter profile is only
 # reported while their hash matches the one it was taken with
 KERNEL_SOURCES = {
-    "dense": ("hc_device.h", "hc_internal.h", "hc_geometry.h", "hc_units.h", "hc_dense.hip"),
+    "dense": ("hc_device.h", "hc_internal.h", "hc_geometry.h", "hc_units.h", "hc_dense.hip",
+              "hc_dense128.hip"),
     "spatial": ("hc_device.h", "hc_internal.h", "hc_geometry.h", "hc_units.h", "hc_spatial.hip"),
 }
 TRAFFIC_FILES = {
