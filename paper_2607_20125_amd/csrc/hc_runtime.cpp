@@ -101,14 +101,29 @@ hc_status fail(hc_ctx *c, hc_status s, const char *fmt, ...) {
   return s;
 }
 
+// A failed HIP call stays the thread's last error until it is read, and the next
+// launch would take it for its own: every failure that is reported or passed over
+// here is read off first.
 #define HC_HIP(ctx, call)                                                               \
   do {                                                                                  \
     hipError_t e_ = (call);                                                             \
-    if (e_ != hipSuccess)                                                               \
+    if (e_ != hipSuccess) {                                                             \
+      (void)hipGetLastError();                                                          \
       return fail(ctx, e_ == hipErrorOutOfMemory ? HC_E_NOMEM : HC_E_DEVICE, "%s: %s", \
                   #call, hipGetErrorString(e_));                                        \
+    }                                                                                   \
   } while (0)
 
+hc_status dev_malloc(hc_ctx *c, DevBuf &b, size_t bytes) {
+  const hipError_t e = hipMalloc(&b.p, bytes);
+  if (e != hipSuccess) {
+    b = DevBuf{};
+    (void)hipGetLastError();
+    return fail(c, HC_E_NOMEM, "hipMalloc(%zu bytes): %s", bytes, hipGetErrorString(e));
+  }
+  b.bytes = bytes;
+  return HC_OK;
+}
 
 void free_buf(DevBuf &b) {
   if (b.p) (void)hipFree(b.p);
@@ -118,14 +133,9 @@ void free_buf(DevBuf &b) {
 hc_status alloc_zero(hc_ctx *c, DevBuf &b, size_t bytes) {
   free_buf(b);
   if (bytes == 0) return HC_OK;
-  hipError_t e = hipMalloc(&b.p, bytes);
-  if (e != hipSuccess) {
-    b.p = nullptr;
-    return fail(c, HC_E_NOMEM, "hipMalloc(%zu bytes): %s", bytes, hipGetErrorString(e));
-  }
-  b.bytes = bytes;
-  e = hipMemset(b.p, 0, bytes);
-  if (e != hipSuccess) return fail(c, HC_E_DEVICE, "hipMemset: %s", hipGetErrorString(e));
+  hc_status st = dev_malloc(c, b, bytes);
+  if (st != HC_OK) return st;
+  HC_HIP(c, hipMemset(b.p, 0, bytes));
   return HC_OK;
 }
 
@@ -153,6 +163,7 @@ hc_status prof_begin(hc_ctx *c, hipStream_t s, EventPair *ep) {
     const hipError_t e = hipEventCreate(&p.b);
     if (e != hipSuccess) {
       (void)hipEventDestroy(p.a);
+      (void)hipGetLastError();
       return fail(c, HC_E_DEVICE, "hipEventCreate: %s", hipGetErrorString(e));
     }
     c->pool.push_back(p);
@@ -247,16 +258,12 @@ hc_status install_types(hc_ctx *c, Layer &l, const uint8_t *types, hipStream_t s
   size_t total = 0;
   for (const DevBuf *b : {&l.k_sd, &l.v_sd, &l.k_g, &l.v_g, &l.k_sp, &l.v_sp}) total += al(b->bytes);
   drop_plan(l);
+  hc_status st;
   if (l.kv.p && l.kv.bytes == total) {
     HC_HIP(c, hipDeviceSynchronize());
   } else {
     free_buf(l.kv);
-    const hipError_t e = hipMalloc(&l.kv.p, total);
-    if (e != hipSuccess) {
-      l.kv.p = nullptr;
-      return fail(c, HC_E_NOMEM, "hipMalloc(%zu bytes): %s", total, hipGetErrorString(e));
-    }
-    l.kv.bytes = total;
+    if ((st = dev_malloc(c, l.kv, total)) != HC_OK) return st;
   }
   l.plan_used = false;
   HC_HIP(c, hipMemsetAsync(l.kv.p, 0, total, s));
@@ -265,7 +272,6 @@ hc_status install_types(hc_ctx *c, Layer &l, const uint8_t *types, hipStream_t s
     b->p = b->bytes ? at : nullptr;
     at += al(b->bytes);
   }
-  hc_status st;
 
   // Spatial work split over key frames when the layer has few Spatial heads
   l.sp_split = c->cfg.spatial_cell > 0 ? 1
@@ -377,12 +383,7 @@ hc_status ensure_plan(hc_ctx *c, Layer &l, int nv) {
   if (!both.empty()) {
     if (l.plan.bytes < both.size()) {
       free_buf(l.plan);
-      const hipError_t e = hipMalloc(&l.plan.p, both.size());
-      if (e != hipSuccess) {
-        l.plan.p = nullptr;
-        return fail(c, HC_E_NOMEM, "hipMalloc(%zu bytes): %s", both.size(), hipGetErrorString(e));
-      }
-      l.plan.bytes = both.size();
+      if ((st = dev_malloc(c, l.plan, both.size())) != HC_OK) return st;
     }
     HC_HIP(c, hipMemcpy(l.plan.p, both.data(), both.size(), hipMemcpyHostToDevice));
   }
@@ -653,10 +654,10 @@ hc_status hc_create(const hc_config *cfg, int device, hc_ctx **out) {
   *out = nullptr;
   if (hc_validate_config(cfg) != HC_OK) return HC_E_INVAL;
   int ndev = 0;
-  if (hipGetDeviceCount(&ndev) != hipSuccess || device < 0 || device >= ndev) return HC_E_DEVICE;
-  if (hipSetDevice(device) != hipSuccess) return HC_E_DEVICE;
   void *scratch = nullptr;
-  if (static_scratch(device, &scratch) != hipSuccess) return HC_E_DEVICE;
+  auto ok = [](hipError_t e) { return e == hipSuccess || ((void)hipGetLastError(), false); };
+  if (!ok(hipGetDeviceCount(&ndev)) || device < 0 || device >= ndev) return HC_E_DEVICE;
+  if (!ok(hipSetDevice(device)) || !ok(static_scratch(device, &scratch))) return HC_E_DEVICE;
   hc_ctx *c = new hc_ctx;
   c->cfg = *cfg;
   c->device = device;
@@ -669,8 +670,7 @@ hc_status hc_create(const hc_config *cfg, int device, hc_ctx **out) {
   c->sd_keys = sd_buffer_keys(cfg->sd_blocks, c->L);
   c->g_keys = global_buffer_keys(cfg->window_blocks, c->L);
   c->sp_keys = (int64_t)cfg->window_blocks * cfg->frames_per_block * c->geo.rows * c->geo.pitch;
-  if (hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, device) != hipSuccess)
-    c->n_cu = 0;
+  if (!ok(hipDeviceGetAttribute(&c->n_cu, hipDeviceAttributeMultiprocessorCount, device))) c->n_cu = 0;
   c->layers.resize(cfg->n_layers);
   if (cfg->spatial_cell > 0) {
     c->cells = build_cell_tables(cfg->grid_h, cfg->grid_w, cfg->frames_per_block,
@@ -1058,11 +1058,13 @@ hc_status hc_classify_heads(hc_ctx *c, int layer, int64_t cur_block, const void 
   // 4. head table + cache split (Sec. 4.3)
   st = hc_set_head_types(c, layer, labels.data(), cur_block, k_win, v_win, stream);
   if (st != HC_OK) return st;
-  std::memcpy(types_out, labels.data(), H);
-  // the routed work list is built while the split runs (a failure here leaves it
-  // to the layer's first hc_attention, which reports it)
-  if (ensure_plan(c, c->layers[layer], W) != HC_OK) c->err.clear();
+  // the routed work list is built while the split runs (without memory for it, that
+  // is left to the layer's first hc_attention)
+  st = ensure_plan(c, c->layers[layer], W);
+  if (st == HC_E_NOMEM) c->err.clear();
+  else if (st != HC_OK) return st;
   HC_HIP(c, hipStreamSynchronize(s));
+  std::memcpy(types_out, labels.data(), H);
   c->cls_done = true;
   return HC_OK;
 }

@@ -1,0 +1,114 @@
+// Checks of the host runtime (hc_runtime.cpp) against a HIP runtime on the CPU
+// (fake_hip.h): what is left after an allocation or a copy failed, and the order
+// of work on different streams.  One check per run, named by the first argument.
+#include <cstdint>
+
+#include "fake_hip.h"
+#include "headcast.h"
+
+static int failures = 0;
+#define CHECK(cond, ...)                                   \
+  do {                                                     \
+    if (!(cond)) {                                         \
+      std::printf("FAIL %s:%d: ", __FILE__, __LINE__);     \
+      std::printf(__VA_ARGS__);                            \
+      std::printf("\n");                                   \
+      ++failures;                                          \
+    }                                                      \
+  } while (0)
+
+namespace {
+
+const hipStream_t kA = (hipStream_t)0x100, kB = (hipStream_t)0x200;
+
+// device memory of the caller: only its address is used
+alignas(16) unsigned char caller_mem[64];
+
+hc_config config(int layers, int heads) {
+  hc_config c;
+  hc_config_default(&c);
+  c.n_layers = layers; c.n_heads = heads; c.head_dim = 64;
+  c.grid_h = 8; c.grid_w = 12; c.frames_per_block = 2; c.window_blocks = 4;
+  c.spatial_radius = 1; c.proxy_radius = 1;
+  return c;
+}
+
+struct Ctx {
+  hc_ctx *c = nullptr;
+  explicit Ctx(const hc_config &cfg) {
+    fake::fail_malloc_in = 0;
+    CHECK(hc_create(&cfg, 0, &c) == HC_OK, "hc_create");
+  }
+  ~Ctx() { hc_destroy(c); }
+  hc_status set(int layer, const std::vector<uint8_t> &t, hipStream_t s = nullptr) {
+    return hc_set_head_types(c, layer, t.data(), 3, caller_mem, caller_mem, s);
+  }
+  hc_status attend(int layer, const std::vector<uint8_t> &t, hipStream_t s = nullptr) {
+    return hc_attention(c, layer, caller_mem, t.data(), (float *)caller_mem, s);
+  }
+  hc_status attend_static(int layer, const std::vector<uint8_t> &t, hipStream_t s = nullptr) {
+    return hc_attention_static(c, layer, caller_mem, t.data(), (float *)caller_mem, s);
+  }
+  hc_status append(int layer, hipStream_t s = nullptr) {
+    return hc_append_block(c, layer, 3, caller_mem, caller_mem, s);
+  }
+  hc_status classify(int layer, std::vector<uint8_t> &t, hipStream_t s = nullptr) {
+    return hc_classify_heads(c, layer, 3, caller_mem, caller_mem, caller_mem, t.data(), nullptr, s);
+  }
+};
+
+const std::vector<uint8_t> kFew = {HC_SINK, HC_DUMMY, HC_SPATIAL, HC_GLOBAL};
+const std::vector<uint8_t> kMany = {HC_GLOBAL, HC_GLOBAL, HC_GLOBAL, HC_GLOBAL};
+const std::vector<uint8_t> kSpatial = {HC_SPATIAL, HC_SPATIAL, HC_SPATIAL, HC_SPATIAL};
+
+// A call that runs out of memory reports it once: the next call, which has
+// nothing to do with it, does not find the error again.  The classification
+// passes over a failed allocation of the routed work list, and over nothing else.
+void errors_are_reported_once() {
+  for (int nth = 1; nth <= 4; ++nth) {
+    Ctx x(config(2, 4));
+    CHECK(x.set(0, kFew) == HC_OK && x.attend(0, kFew) == HC_OK, "first layer");
+    fake::fail_malloc_in = nth;
+    const hc_status st = x.set(1, kMany);
+    fake::fail_malloc_in = 0;
+    CHECK(st == HC_OK || st == HC_E_NOMEM, "status %d", st);
+    CHECK(x.append(0) == HC_OK, "append after failure %d: %s", nth, hc_last_error(x.c));
+  }
+  int passed_over = 0;
+  for (int nth = 1; nth <= 24; ++nth) {
+    Ctx x(config(2, 4));
+    CHECK(x.set(0, kFew) == HC_OK, "first layer");
+    std::vector<uint8_t> t(4);
+    fake::fail_malloc_in = nth;
+    const hc_status st = x.classify(1, t);
+    passed_over += st == HC_OK && fake::fail_malloc_in == 0;
+    fake::fail_malloc_in = 0;
+    CHECK(st == HC_OK || st == HC_E_NOMEM, "status %d", st);
+    CHECK(x.append(0) == HC_OK, "append after failure %d: %s", nth, hc_last_error(x.c));
+    if (st == HC_OK) CHECK(x.attend(1, t) == HC_OK, "layer 1 after failure %d: %s", nth, hc_last_error(x.c));
+  }
+  CHECK(passed_over > 0, "no failure left the classification without a work list");
+  Ctx x(config(2, 4));
+  std::vector<uint8_t> t(4);
+  CHECK(x.classify(0, t) == HC_OK, "classification");
+  fake::fail_memcpy = hipErrorInvalidValue;      // the routed work list's upload
+  CHECK(x.classify(1, t) == HC_E_DEVICE, "a failed upload is not passed over");
+  CHECK(x.append(0) == HC_OK, "append: %s", hc_last_error(x.c));
+}
+
+struct { const char *name; void (*run)(); } checks[] = {
+    {"errors_are_reported_once", errors_are_reported_once},
+};
+
+}  // namespace
+
+int main(int argc, char **argv) {
+  for (auto &c : checks) {
+    if (argc > 1 && std::strcmp(argv[1], c.name) != 0) continue;
+    c.run();
+    for (size_t i = 0; i < fake::faults.size() && i < 20; ++i) std::printf("FAULT %s\n", fake::faults[i].c_str());
+    if (failures || !fake::faults.empty()) return 1;
+    std::printf("%s: ok\n", c.name);
+  }
+  return 0;
+}
