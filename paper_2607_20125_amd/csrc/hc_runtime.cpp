@@ -41,6 +41,7 @@ struct Layer {
   const CombineItem *comb = nullptr;
   int n_units = 0, n_comb = 0;
   int64_t plan_tiles = 0;      // key tiles of all units
+  int64_t plan_slots = 0;      // partial slots that the units write
   int plan_nv = -1;            // valid window blocks the plan was built for
   bool plan_used = false;      // launches may still read the plan's memory
   int static_nv = -1;          // window fill that static_parts was chosen for
@@ -228,6 +229,33 @@ uint16_t *sp_frames(const hc_ctx *c, const DevBuf &b) {
   return b.p ? (uint16_t *)b.p + sp_lead(c) * c->cfg.head_dim : nullptr;
 }
 
+// The partial results that all layers share: at least `slots` dense slots, and at
+// least `rows` rows of Spatial splits.  The old memory is released before the new is
+// allocated, so while that fails there is none: the counts say so, and the next
+// hc_attention of any layer asks again.
+hc_status need_part(hc_ctx *c, int64_t slots) {
+  if (slots <= c->part_slots) return HC_OK;
+  HC_HIP(c, hipDeviceSynchronize());
+  c->part_slots = 0;
+  hc_status st = alloc_zero(c, c->part, (size_t)slots * partial_floats(c->cfg.head_dim) * 4);
+  if (st == HC_OK) c->part_slots = slots;
+  return st;
+}
+
+hc_status need_sp_part(hc_ctx *c, int64_t rows) {
+  if (rows <= c->sp_part_rows) return HC_OK;
+  HC_HIP(c, hipDeviceSynchronize());
+  c->sp_part_rows = 0;
+  hc_status st = alloc_zero(c, c->sp_part, (size_t)rows * c->cfg.head_dim * 4);
+  if (st == HC_OK) st = alloc_zero(c, c->sp_ml, (size_t)rows * 2 * 4);
+  if (st == HC_OK) c->sp_part_rows = rows;
+  return st;
+}
+
+int64_t sp_split_rows(const hc_ctx *c, const Layer &l) {
+  return l.sp_split > 1 ? (int64_t)l.sp_split * (int64_t)l.sp_heads.size() * c->L : 0;
+}
+
 // Build the layer's head table and its compact buffers, zeroed on `s`.  The six
 // buffers are one allocation, which is kept when the new table needs exactly as
 // many bytes; either way everything that read the old buffers is over before
@@ -276,24 +304,12 @@ hc_status install_types(hc_ctx *c, Layer &l, const uint8_t *types, hipStream_t s
   // Spatial work split over key frames when the layer has few Spatial heads
   l.sp_split = c->cfg.spatial_cell > 0 ? 1
                                          : spatial_split(c, (int)l.sp_heads.size(), c->cfg.spatial_radius);
-  if (l.sp_split > 1) {
-    const int64_t rows = (int64_t)l.sp_split * l.sp_heads.size() * c->L;
-    if (rows > c->sp_part_rows) {
-      HC_HIP(c, hipDeviceSynchronize());
-      if ((st = alloc_zero(c, c->sp_part, (size_t)rows * D * 4)) != HC_OK) return st;
-      if ((st = alloc_zero(c, c->sp_ml, (size_t)rows * 2 * 4)) != HC_OK) return st;
-      c->sp_part_rows = rows;
-    }
-  }
+  if ((st = need_sp_part(c, sp_split_rows(c, l))) != HC_OK) return st;
   // partial slots for the largest plan of this layer (full window)
   const int64_t nqt = (c->L + kQTile - 1) / kQTile;
   const int64_t need = ((int64_t)l.g_heads.size() * c->cfg.window_blocks +
                         (int64_t)l.sd_heads.size() * (c->cfg.sd_blocks == 2 ? 2 : 0)) * nqt;
-  if (need > c->part_slots) {
-    HC_HIP(c, hipDeviceSynchronize());
-    if ((st = alloc_zero(c, c->part, (size_t)need * partial_floats(D) * 4)) != HC_OK) return st;
-    c->part_slots = need;
-  }
+  if ((st = need_part(c, need)) != HC_OK) return st;
   l.has_types = true;
   return HC_OK;
 }
@@ -368,12 +384,7 @@ hc_status ensure_plan(hc_ctx *c, Layer &l, int nv) {
   hc_status st;
   int64_t slots = 0;
   for (const CombineItem &it : comb) slots = std::max<int64_t>(slots, (int64_t)it.slot0 + it.n_slots);
-  if (slots > c->part_slots) {
-    HC_HIP(c, hipDeviceSynchronize());
-    if ((st = alloc_zero(c, c->part, (size_t)slots * partial_floats(c->cfg.head_dim) * 4)) != HC_OK)
-      return st;
-    c->part_slots = slots;
-  }
+  if ((st = need_part(c, slots)) != HC_OK) return st;
   // both lists in one copy
   const size_t b_units = (units.size() * sizeof(DenseUnit) + 255) / 256 * 256;
   std::vector<unsigned char> both(b_units + comb.size() * sizeof(CombineItem));
@@ -393,6 +404,7 @@ hc_status ensure_plan(hc_ctx *c, Layer &l, int nv) {
   l.n_comb = (int)comb.size();
   l.plan_tiles = 0;
   for (const DenseUnit &u : units) l.plan_tiles += plan_detail::unit_tiles(u);
+  l.plan_slots = slots;
   l.plan_nv = nv;
   l.plan_used = true;
   return HC_OK;
@@ -785,6 +797,8 @@ hc_status hc_attention(hc_ctx *c, int layer, const void *q, const uint8_t *head_
   HC_HIP(c, hipSetDevice(c->device));
   const int nv = n_valid_blocks(c, l.cur_block);
   if ((st = ensure_plan(c, l, nv)) != HC_OK) return st;
+  if ((st = need_part(c, l.plan_slots)) != HC_OK) return st;
+  if ((st = need_sp_part(c, sp_split_rows(c, l))) != HC_OK) return st;
   LayerWork wk;
   wk.units = l.units;
   wk.n_units = l.n_units;

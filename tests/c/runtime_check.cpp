@@ -96,8 +96,40 @@ void errors_are_reported_once() {
   CHECK(x.append(0) == HC_OK, "append: %s", hc_last_error(x.c));
 }
 
+// A layer that works keeps working when another layer's call runs out of memory
+// while it replaces the buffers that all layers share.
+void shared_buffers_after_failed_growth() {
+  for (const auto &more : {kMany, kSpatial})
+    for (int nth = 1; nth <= 6; ++nth) {
+      Ctx x(config(2, 4));
+      CHECK(x.set(0, kFew) == HC_OK && x.attend(0, kFew) == HC_OK, "first layer");
+      fake::fail_malloc_in = nth;
+      const hc_status st = x.set(1, more);
+      if (st == HC_OK) (void)x.attend(1, more);
+      fake::fail_malloc_in = 0;
+      CHECK(st == HC_OK || st == HC_E_NOMEM, "status %d", st);
+      CHECK(x.attend(0, kFew) == HC_OK, "layer 0 after failure %d: %s", nth, hc_last_error(x.c));
+      CHECK(x.set(1, more) == HC_OK && x.attend(1, more) == HC_OK, "layer 1 again");
+      CHECK(x.attend(0, kFew) == HC_OK, "layer 0 again");
+    }
+  for (int nth = 1; nth <= 24; ++nth) {          // the classification's own growth
+    hc_config cfg = config(2, 4);
+    cfg.theta_sink = cfg.theta_dummy = cfg.theta_spatial = 2.f;   // every head Global
+    Ctx x(cfg);
+    CHECK(x.set(0, kFew) == HC_OK && x.attend(0, kFew) == HC_OK, "first layer");
+    std::vector<uint8_t> t(4);
+    fake::fail_malloc_in = nth;
+    const hc_status st = x.classify(1, t);
+    fake::fail_malloc_in = 0;
+    CHECK(st == HC_OK || st == HC_E_NOMEM, "status %d", st);
+    CHECK(x.attend(0, kFew) == HC_OK, "layer 0 after failure %d: %s", nth, hc_last_error(x.c));
+    if (st == HC_OK) CHECK(x.attend(1, t) == HC_OK, "layer 1 after failure %d", nth);
+  }
+}
+
 struct { const char *name; void (*run)(); } checks[] = {
     {"errors_are_reported_once", errors_are_reported_once},
+    {"shared_buffers_after_failed_growth", shared_buffers_after_failed_growth},
 };
 
 }  // namespace
