@@ -43,7 +43,6 @@ struct Layer {
   int64_t plan_tiles = 0;      // key tiles of all units
   int64_t plan_slots = 0;      // partial slots that the units write
   int plan_nv = -1;            // valid window blocks the plan was built for
-  bool plan_used = false;      // launches may still read the plan's memory
   int static_nv = -1;          // window fill that static_parts was chosen for
   int static_parts = 0;        // key ranges per Global head of the device-built work list
   int sp_split = 1;            // key-frame split of the Spatial work (full window)
@@ -137,6 +136,8 @@ hc_status alloc_zero(hc_ctx *c, DevBuf &b, size_t bytes) {
   hc_status st = dev_malloc(c, b, bytes);
   if (st != HC_OK) return st;
   HC_HIP(c, hipMemset(b.p, 0, bytes));
+  // waited for: the caller's stream need not be ordered after the null stream
+  HC_HIP(c, hipStreamSynchronize(nullptr));
   return HC_OK;
 }
 
@@ -152,7 +153,6 @@ void free_layer(Layer &l) {
   free_buf(l.plan);
   l.k_sd = l.v_sd = l.k_g = l.v_g = l.k_sp = l.v_sp = DevBuf{};
   drop_plan(l);
-  l.plan_used = false;
 }
 
 // --- profiling ----------------------------------------------------------------
@@ -293,7 +293,6 @@ hc_status install_types(hc_ctx *c, Layer &l, const uint8_t *types, hipStream_t s
     free_buf(l.kv);
     if ((st = dev_malloc(c, l.kv, total)) != HC_OK) return st;
   }
-  l.plan_used = false;
   HC_HIP(c, hipMemsetAsync(l.kv.p, 0, total, s));
   unsigned char *at = (unsigned char *)l.kv.p;
   for (DevBuf *b : {&l.k_sd, &l.v_sd, &l.k_g, &l.v_g, &l.k_sp, &l.v_sp}) {
@@ -375,12 +374,12 @@ hc_status ensure_plan(hc_ctx *c, Layer &l, int nv) {
                   (long long)unit_region_keys(u, regions, D));
     }
   }
-  // launches of the previous plan are over before its memory is written again
-  if (l.plan_used) HC_HIP(c, hipDeviceSynchronize());
+  // launches of the previous plan are over before its memory is written again, and
+  // so is the split or append that this window fill comes from, on whatever stream
+  if (!units.empty()) HC_HIP(c, hipDeviceSynchronize());
   // no plan until this one is complete: a failure below leaves a rebuild for
   // the next call instead of a list that does not match its counts
   drop_plan(l);
-  l.plan_used = false;
   hc_status st;
   int64_t slots = 0;
   for (const CombineItem &it : comb) slots = std::max<int64_t>(slots, (int64_t)it.slot0 + it.n_slots);
@@ -406,7 +405,6 @@ hc_status ensure_plan(hc_ctx *c, Layer &l, int nv) {
   for (const DenseUnit &u : units) l.plan_tiles += plan_detail::unit_tiles(u);
   l.plan_slots = slots;
   l.plan_nv = nv;
-  l.plan_used = true;
   return HC_OK;
 }
 

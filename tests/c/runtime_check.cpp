@@ -127,9 +127,29 @@ void shared_buffers_after_failed_growth() {
   }
 }
 
+// The first hc_attention at a window fill synchronises: a table set on one stream is
+// attended from another.  Memory that a call clears is clear before the caller's
+// stream uses it.
+void first_attention_on_another_stream() {
+  for (const auto &t : {kFew, kMany}) {
+    Ctx x(config(1, 4));
+    CHECK(x.set(0, t, kA) == HC_OK && x.attend(0, t, kB) == HC_OK, "%s", hc_last_error(x.c));
+    (void)hipDeviceSynchronize();
+  }
+  // (a layer without dense work has no list to build: its first call only launches)
+  Ctx y(config(1, 4));
+  CHECK(y.set(0, kSpatial, kA) == HC_OK && y.attend(0, kSpatial, kA) == HC_OK, "%s", hc_last_error(y.c));
+  (void)hipDeviceSynchronize();
+  Ctx x(config(1, 4));
+  std::vector<uint8_t> t(4);
+  CHECK(x.classify(0, t, kA) == HC_OK && x.attend(0, t, kB) == HC_OK, "%s", hc_last_error(x.c));
+  (void)hipDeviceSynchronize();
+}
+
 struct { const char *name; void (*run)(); } checks[] = {
     {"errors_are_reported_once", errors_are_reported_once},
     {"shared_buffers_after_failed_growth", shared_buffers_after_failed_growth},
+    {"first_attention_on_another_stream", first_attention_on_another_stream},
 };
 
 }  // namespace
