@@ -253,8 +253,10 @@ inline HC_HD CombineItem static_comb_item(const StaticPlan &p, int i) {
 // ranges' partials takes longer than the tiles it saves: append and attention of
 // six Global and six Sink/Dummy heads, one range against one per block, take 19.5
 // against 22.0 us at 8 tiles, 20.0 against 22.0 at 12 and 23.6 against 22.4 at 16;
-// 64-dim heads 19.5 against 22.4 at 16 and 22.4 both at 32.  (Not asked where the
-// layer's Spatial heads need the merge launch anyway.)
+// 64-dim heads 19.5 against 22.4 at 16 and 22.4 both at 32.  (Not asked where split
+// Spatial heads or two-block Sink/Dummy heads bring the merge launch anyway: with
+// three blocks of 256 tokens and two-block heads one range took 25.8 us, one per
+// block 22.2.)
 inline int global_parts(int d, int L, int nv) {
   return ((int64_t)nv * L + kKTile - 1) / kKTile <= (d == 64 ? 24 : 12) ? 1 : nv;
 }

@@ -313,6 +313,12 @@ hc_status install_types(hc_ctx *c, Layer &l, const uint8_t *types, hipStream_t s
   return HC_OK;
 }
 
+// Whether a layer-step has partials to merge however its Global heads are cut: those of
+// split Spatial heads, or of two-block Sink/Dummy heads.
+bool merged_anyway(const hc_ctx *c, const Layer &l, int nv) {
+  return l.sp_split > 1 || (c->cfg.sd_blocks == 2 && nv >= 2 && !l.sd_heads.empty());
+}
+
 // Dense work of one layer with `nv` valid window blocks (hc_plan.h).
 void plan_units(const hc_ctx *c, const Layer &l, int nv, std::vector<DenseUnit> &units,
                 std::vector<CombineItem> &comb) {
@@ -327,7 +333,7 @@ void plan_units(const hc_ctx *c, const Layer &l, int nv, std::vector<DenseUnit> 
   DensePlanShape shape;
   shape.L = c->L;
   shape.nv = nv;
-  shape.g_parts = l.sp_split > 1 ? 0 : global_parts(D, c->L, nv);
+  shape.g_parts = merged_anyway(c, l, nv) ? 0 : global_parts(D, c->L, nv);
   shape.sd_blocks = c->cfg.sd_blocks;
   shape.F = c->cfg.frames_per_block;
   shape.grid_h = c->cfg.grid_h;
@@ -850,7 +856,8 @@ hc_status hc_attention_static(hc_ctx *c, int layer, const void *q, const uint8_t
                            al(((size_t)p.n_g + p.n_sd) * p.nqt * sizeof(CombineItem));
     const int64_t max_slots =
         longest + 256 < kStaticScratchBytes ? (kStaticScratchBytes - longest - 256) / slot_bytes : 0;
-    l.static_parts = static_global_parts(p, c->n_cu, dense_groups_per_cu(D), max_slots, l.sp_split > 1);
+    l.static_parts = static_global_parts(p, c->n_cu, dense_groups_per_cu(D), max_slots,
+                                          merged_anyway(c, l, nv));
     l.static_nv = nv;
   }
   p.g_parts = l.static_parts;

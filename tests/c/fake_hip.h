@@ -31,6 +31,7 @@ inline int fail_malloc_in = 0;        // n: the n-th hipMalloc from now fails
 inline hipError_t fail_memcpy = hipSuccess;   // the next hipMemcpy fails with this
 inline int launches = 0, syncs = 0;
 inline bool dense_wide = false;       // of the last dense launch
+inline int dense_units = 0;           // its units with work
 
 inline hipError_t ret(hipError_t e) {
   if (e != hipSuccess) last = e;
@@ -135,10 +136,12 @@ hipError_t launch_dense(const DenseArgs &a, int d, DenseRole, hipStream_t s) {
   fake::dense_wide = a.wide_waves;
   touch("dense work list", a.units, a.n_units * sizeof(DenseUnit), s, false);
   if (!fake::owner(a.units, a.n_units * sizeof(DenseUnit))) return fake::take_last();
+  fake::dense_units = 0;
   int64_t slots = 0;
   for (int i = 0; i < a.n_units; ++i) {
     const DenseUnit &u = a.units[i];
     if (u.head < 0) continue;
+    ++fake::dense_units;
     slots = std::max<int64_t>(slots, u.slot + 1);
     const int64_t end = u.kv0 + (u.kv1 - u.kv0 + kKTile - 1) / kKTile * kKTile;
     touch("dense keys", u.k, end * d * 2, s, false);

@@ -146,10 +146,33 @@ void first_attention_on_another_stream() {
   (void)hipDeviceSynchronize();
 }
 
+// Small Global windows are one unit per query tile, except where other partials of
+// the layer are merged anyway: two-block Sink/Dummy heads, split Spatial heads.
+void small_windows() {
+  const std::vector<uint8_t> dense = {HC_GLOBAL, HC_SINK, HC_DUMMY, HC_GLOBAL};
+  for (int sd = 1; sd <= 2; ++sd)
+    for (const auto &t : {dense, kMany, kFew}) {
+      hc_config cfg = config(1, 4);
+      cfg.frames_per_block = 1;                   // 96 tokens: one query tile, six key tiles
+      cfg.sd_blocks = sd;
+      Ctx x(cfg);
+      int n[4] = {};
+      for (uint8_t k : t) ++n[k];
+      const int n_sd = n[HC_SINK] + n[HC_DUMMY];
+      const int per_global = (sd == 2 && n_sd > 0) || n[HC_SPATIAL] > 0 ? 4 : 1;
+      const int want = n[HC_GLOBAL] * per_global + n_sd * sd;
+      CHECK(x.set(0, t) == HC_OK && x.attend(0, t) == HC_OK, "%s", hc_last_error(x.c));
+      CHECK(fake::dense_units == want, "hc_attention: %d units, not %d", fake::dense_units, want);
+      CHECK(x.attend_static(0, t) == HC_OK, "%s", hc_last_error(x.c));
+      CHECK(fake::dense_units == want, "hc_attention_static: %d units, not %d", fake::dense_units, want);
+    }
+}
+
 struct { const char *name; void (*run)(); } checks[] = {
     {"errors_are_reported_once", errors_are_reported_once},
     {"shared_buffers_after_failed_growth", shared_buffers_after_failed_growth},
     {"first_attention_on_another_stream", first_attention_on_another_stream},
+    {"small_windows", small_windows},
 };
 
 }  // namespace
