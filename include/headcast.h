@@ -250,7 +250,10 @@ hc_status hc_attention(hc_ctx *ctx, int layer, const void *q, const uint8_t *hea
  * partials of Spatial heads live in one fixed array of HC_STATIC_SCRATCH_BYTES
  * per GPU, held by the library until the process ends (Spatial and other
  * partials take turns in the same place where not both fit); the work list is
- * written by a kernel on `stream` at every call.  Every call on a GPU uses
+ * written by a kernel on `stream` at every call.  The key ranges of that list are
+ * chosen on the host by the first call at a window fill (some microseconds, up to
+ * about 50 for layers that run 150 and more; layers with as many heads of each kind
+ * share the choice).  Every call on a GPU uses
  * that GPU's array and leaves its contents behind, so calls that overlap on
  * one GPU (other streams, other contexts, other threads) race and must be
  * ordered by the caller.  A layer whose work needs more than the array holds

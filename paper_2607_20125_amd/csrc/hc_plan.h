@@ -199,6 +199,22 @@ inline HC_HD int static_n_slots(const StaticPlan &p) {
   return ((gp > 1 ? p.n_g * gp : 0) + (p.sd_parts > 1 ? p.n_sd * p.sd_parts : 0)) * p.nqt;
 }
 
+// Its place in the scratch: units, merge items and partial slots, each 256-byte aligned.
+inline size_t align256(size_t b) { return (b + 255) / 256 * 256; }
+inline size_t static_list_bytes(const StaticPlan &p) {
+  return align256((size_t)static_n_units(p) * sizeof(DenseUnit)) +
+         align256((size_t)static_n_comb(p) * sizeof(CombineItem));
+}
+inline size_t static_dense_bytes(const StaticPlan &p) {
+  return static_list_bytes(p) + align256((size_t)static_n_slots(p) * partial_floats(p.d) * sizeof(float));
+}
+// Slots that fit beside the longest list, of kMaxSrcBlocks ranges per Global head.
+inline int64_t static_max_slots(StaticPlan p, size_t scratch) {
+  p.g_parts = kMaxSrcBlocks;
+  const size_t list = static_list_bytes(p) + 256;
+  return list < scratch ? (int64_t)((scratch - list) / ((size_t)partial_floats(p.d) * sizeof(float))) : 0;
+}
+
 inline HC_HD DenseUnit static_dense_unit(const StaticPlan &p, int i) {
   DenseUnit u{};
   const int gp = static_g_parts(p);
@@ -537,48 +553,171 @@ inline void balance_units(int n_cu, std::vector<DenseUnit> &units, std::vector<C
   }
 }
 
-// Key ranges per Global head of a work list that is not tail-balanced (the
-// device-built one): the number whose runs end first, counting the merge of its
-// partial slots, with at most max_slots slots.  One range per window block may
-// leave the last round of a run nearly empty (480P, three Global and seven
-// Sink/Dummy heads: 1036 units on 512 slots, three rounds of 73 tiles; six ranges
-// give 925 units of at most 86 tiles in two).  One range per block stays unless
-// another number ends at least 2% earlier.
-inline int static_global_parts(StaticPlan p, int n_cu, int groups_per_cu, int64_t max_slots,
-                               bool merged_anyway) {
-  using namespace plan_detail;
-  const int small = merged_anyway ? p.nv : global_parts(p.d, p.L, p.nv);
-  if (p.n_g == 0 || n_cu <= 0 || n_cu % 8 != 0 || small < p.nv) return small;
-  // in key tiles of a full launch (1.8 us each): a merge launch, and 66 KB a
-  // slot written and read at 4 TB/s
-  constexpr double kMergeTiles = 2.5, kSlotTiles = 0.018;
-  const int slots = groups_per_cu * n_cu / 8;
-  double best = 0;
-  int best_parts = p.nv;
-  auto end_of = [&](int parts, double most) {   // not counted further than `most`
-    p.g_parts = parts;
-    const int n = static_n_units(p), per = n / 8, rem = n % 8;
-    double end = 0;
-    for (int x = 0; x < 8; ++x) {
-      const int b = x * per + std::min(x, rem), e = b + per + (x < rem ? 1 : 0);
-      SlotClock clock(slots);
-      for (int i = b; i < e && clock.end < most; ++i)
-        clock.add(unit_tiles(static_dense_unit(p, i)) + kUnitOverheadTiles);
-      end = std::max(end, clock.end);
-      if (end >= most) break;
+// ---------------------------------------------------------------------------
+// How long a dense launch takes, from its work list: every XCD runs its part of the
+// list in order on its CUs, and work groups that share a CU share its rate, so the
+// time follows the end with one slot per CU.  Where the last groups are alone on
+// their CUs they do not reach the full rate, by which it leans towards the end with
+// two slots (`lone`; the kernel with one wave per SIMD gets half the rate alone, so
+// for it two slots are the whole answer).  A unit costs its key tiles and a fixed
+// number of tiles on top.  Fitted to forced key ranges on both 128-dim kernels and
+// the 64-dim one (45 layers of 440 to 10800 tokens, 1 to 8 blocks, 1 to 16 Global
+// heads, 1 to 16 ranges: some 700 times, 3-4% rms).
+// ---------------------------------------------------------------------------
+struct DenseCost {
+  double tile_us;      // a key tile of 128 queries on a CU
+  double unit_tiles;   // fixed cost of a unit in tiles
+  double lone;
+};
+inline constexpr DenseCost kCost64 = {0.369, 4.0, 0.2};
+inline constexpr DenseCost kCost128 = {0.619, 2.0, 0.2};        // 32 queries per wave
+inline constexpr DenseCost kCostWide128 = {0.564, 4.0, 1.0};    // 64 queries per wave
+
+// A merge launch, and one slot's way through memory (33 and 66 KB), in us.
+inline constexpr double merge_launch_us(int d) { return d == 64 ? 4.0 : 5.3; }
+inline constexpr double merge_slot_us(int d) { return d == 64 ? 0.0070 : 0.0202; }
+
+// When the slots of an XCD are free, as groups of slots with the same time: `count`
+// units of one cost go to the slots that are free first, a group at a time.
+struct SlotGroups {
+  static constexpr int kMax = 256;
+  double at[kMax];     // ascending
+  int n[kMax];
+  int groups = 1;
+  double end = 0.0;
+  explicit SlotGroups(int slots) { at[0] = 0.0; n[0] = slots; }
+  void add(double cost, int64_t count) {
+    while (count > 0) {
+      const int k = (int)std::min<int64_t>(count, n[0]);
+      const double t = at[0] + cost;
+      if (k < n[0]) {
+        n[0] -= k;
+      } else {
+        --groups;
+        std::copy(at + 1, at + 1 + groups, at);
+        std::copy(n + 1, n + 1 + groups, n);
+      }
+      int i = groups;
+      while (i > 0 && at[i - 1] > t) --i;
+      if (i > 0 && at[i - 1] == t) {
+        n[i - 1] += k;
+      } else {
+        std::copy_backward(at + i, at + groups, at + groups + 1);
+        std::copy_backward(n + i, n + groups, n + groups + 1);
+        at[i] = t;
+        n[i] = k;
+        ++groups;
+      }
+      end = std::max(end, t);
+      count -= k;
     }
+  }
+};
+
+// Time of a launch of n_units units in list order.  tiles(i, &same): the key tiles of
+// unit i (0: padding) and how many units from i on have as many.
+template <class Tiles>
+inline double dense_us(const DenseCost &c, int n_units, int n_cu, Tiles &&tiles) {
+  const int cus = n_cu / 8, per = n_units / 8, rem = n_units % 8;
+  double one = 0.0, two = 0.0;
+  for (int x = 0; x < 8; ++x) {
+    const int b = x * per + std::min(x, rem), e = b + per + (x < rem ? 1 : 0);
+    SlotGroups g1(cus), g2(2 * cus);
+    bool alike = true;
+    for (int i = b, same = 0; i < e; i += same) {
+      const int nt = tiles(i, &same);
+      alike = alike && i == b && same >= n_units - b;
+      same = std::min(same, e - i);
+      if (nt == 0) continue;
+      if (c.lone < 1.0) g1.add(nt + c.unit_tiles, same);
+      g2.add(nt + c.unit_tiles, same);
+    }
+    one = std::max(one, g1.end);
+    two = std::max(two, g2.end);
+    if (alike) break;            // the runs after this one hold the same units, and no more
+  }
+  return c.tile_us * ((1.0 - c.lone) * one + c.lone * 2.0 * two);
+}
+
+// Device counts that the estimates cover.
+inline bool dense_us_covers(int n_cu) {
+  return n_cu > 0 && n_cu % 8 == 0 && n_cu / 4 <= SlotGroups::kMax;
+}
+
+// The device-built work list of the no-allocation call: its key ranges per Global head
+// and the kernel it runs on.
+struct StaticChoice {
+  int parts;
+  bool wide;
+};
+
+inline double static_dense_us(const StaticPlan &p, const DenseCost &c, int n_cu) {
+  const int gp = static_g_parts(p), ng = p.n_g * gp * p.nqt, n = static_n_units(p);
+  const bool equal = gp == 1 || gp == p.nv;
+  return dense_us(c, n, n_cu, [&](int i, int *same) {
+    if (i >= ng) {
+      *same = n - i;
+      return (p.L + kKTile - 1) / kKTile;
+    }
+    *same = equal ? ng - i : p.nqt - i % p.nqt;
+    int32_t kv0, kv1;
+    global_part(p.L, p.nv, gp, (i / p.nqt) % gp, &kv0, &kv1);
+    const int nt = (kv1 - kv0 + kKTile - 1) / kKTile;
+    if (equal && nt == (p.L + kKTile - 1) / kKTile) *same = n - i;
+    return nt;
+  });
+}
+
+// This list is not tail-balanced, so its last round may be nearly empty; other ranges
+// than one per block then end earlier (480P, three Global, seven Sink/Dummy and two
+// Spatial heads: 1036 units in three rounds of 512 take 373 us, six ranges 350, and
+// 334 with 64 queries per wave), and so may waves of 32 queries (four Global and eight
+// Sink/Dummy heads of two 480P blocks: 203 against 231 us).  The estimate decides
+// both, with at most max_slots partial slots.  One range per block stays unless
+// another count is 2% faster, and 7% where that is fewer, longer ranges with 64
+// queries per wave: those are estimated up to 6% too fast (6912 tokens, four blocks,
+// three ranges 473 us against 469).  15 us stand for the rest of the call.  Windows
+// that hc_attention leaves uncut are left uncut here.  Counts whose perfectly packed
+// list would not be faster are passed over unsimulated: 0-50 us a choice on one CPU
+// (30-420 us with every count simulated unit by unit).
+inline StaticChoice static_choice(StaticPlan p, int n_cu, int64_t max_slots, bool merged_anyway) {
+  constexpr double kGain = 0.02, kWideLongGain = 0.07, kRest = 15.0;
+  const int small = merged_anyway ? p.nv : global_parts(p.d, p.L, p.nv);
+  const int64_t l_tiles = (p.L + kKTile - 1) / kKTile, w_tiles = ((int64_t)p.nv * p.L + kKTile - 1) / kKTile;
+  const int64_t tiles = (p.n_g * w_tiles + (int64_t)p.n_sd * p.sd_parts * l_tiles) * p.nqt;
+  const bool may_wide = p.d == 128 && dense_wide_waves(tiles, n_cu);
+  if (!dense_us_covers(n_cu) || static_n_units(p) == 0) return {small, may_wide};
+  const DenseCost &cost = p.d == 64 ? kCost64 : kCost128;
+  auto merge_us = [&] {
     const int ns = static_n_slots(p);
-    return end + (ns > 0 ? kMergeTiles + kSlotTiles * ns : 0.0);
+    return (ns > 0 || merged_anyway ? merge_launch_us(p.d) : 0.0) + ns * merge_slot_us(p.d);
   };
-  best = end_of(p.nv, 1e30);
-  const int64_t tiles = ((int64_t)p.nv * p.L + kKTile - 1) / kKTile;
-  for (int parts = 1; parts <= std::min<int64_t>(kMaxSrcBlocks, tiles); ++parts) {
+  auto packed_us = [&](const DenseCost &c) {
+    return c.tile_us * (tiles + c.unit_tiles * static_n_units(p)) / n_cu;
+  };
+  StaticChoice best = {small, false};
+  double best_us = 1e30;
+  auto take = [&](const DenseCost &c, bool wide, double at_most) {   // p.g_parts on this kernel
+    if (packed_us(c) + merge_us() >= at_most) return;
+    const double t = static_dense_us(p, c, n_cu) + merge_us();
+    if (t < at_most) { best = {p.g_parts, wide}; best_us = t; }
+  };
+  p.g_parts = small;
+  take(cost, false, best_us);
+  if (may_wide) take(kCostWide128, true, best_us);
+  if (p.n_g == 0 || small < p.nv) return best;
+  const double base_us = best_us;
+  for (int parts = 1; parts <= std::min<int64_t>(kMaxSrcBlocks, w_tiles); ++parts) {
     p.g_parts = parts;
     if (parts == p.nv || static_n_slots(p) > max_slots) continue;
-    const double t = end_of(parts, best);
-    if (t < best * 0.98) { best = t; best_parts = parts; }
+    const double at_most = best_us - kGain * (best_us + kRest);
+    take(cost, false, at_most);
+    if (may_wide)
+      take(kCostWide128, true,
+           std::min(best.parts == parts ? best_us : at_most,
+                    parts < p.nv ? base_us - kWideLongGain * (base_us + kRest) : 1e30));
   }
-  return best_parts;
+  return best;
 }
 
 }  // namespace hc

@@ -43,8 +43,8 @@ struct Layer {
   int64_t plan_tiles = 0;      // key tiles of all units
   int64_t plan_slots = 0;      // partial slots that the units write
   int plan_nv = -1;            // valid window blocks the plan was built for
-  int static_nv = -1;          // window fill that static_parts was chosen for
-  int static_parts = 0;        // key ranges per Global head of the device-built work list
+  int static_nv = -1;          // window fill that `chosen` is for
+  StaticChoice chosen{};       // the device-built work list
   int sp_split = 1;            // key-frame split of the Spatial work (full window)
 };
 
@@ -83,6 +83,14 @@ struct hc_ctx {
   int cls_n_units = 0, cls_n_comb = 0;
   bool cls_done = false;       // cls_o holds the outputs of a successful classification
   void *scratch = nullptr;     // this device's fixed scratch (hc_attention_static)
+  // the last choices of hc_attention_static: layers with as many heads of each kind
+  // at the same window fill share one
+  struct {
+    int n_g, n_sd, nv;
+    bool merged;
+    StaticChoice choice;
+  } static_memo[16];
+  int static_memos = 0;        // choices made
 };
 
 namespace {
@@ -507,12 +515,24 @@ hc_status check_attention(hc_ctx *c, int layer, const void *q, const uint8_t *he
   return HC_OK;
 }
 
+StaticChoice static_choice_shared(hc_ctx *c, const StaticPlan &p, bool merged) {
+  constexpr int kMemos = (int)(sizeof c->static_memo / sizeof c->static_memo[0]);
+  for (int i = 0; i < std::min(c->static_memos, kMemos); ++i) {
+    const auto &m = c->static_memo[i];
+    if (m.n_g == p.n_g && m.n_sd == p.n_sd && m.nv == p.nv && m.merged == merged) return m.choice;
+  }
+  const StaticChoice choice = static_choice(p, c->n_cu, static_max_slots(p, kStaticScratchBytes), merged);
+  c->static_memo[c->static_memos % kMemos] = {p.n_g, p.n_sd, p.nv, merged, choice};
+  c->static_memos = c->static_memos < 2 * kMemos - 1 ? c->static_memos + 1 : kMemos;
+  return choice;
+}
+
 // Device memory one routed layer-step works in: the dense work list and merge
 // items, the partial-result slots, and the Spatial split partials.
 struct LayerWork {
   const DenseUnit *units = nullptr;
   int n_units = 0;
-  int64_t tiles = 0;           // key tiles of all units
+  bool wide_waves = false;     // 128-dim heads: 64 queries per wave
   const CombineItem *comb = nullptr;
   int n_comb = 0;
   float *part = nullptr;
@@ -584,7 +604,7 @@ hc_status run_layer(hc_ctx *c, const Layer &l, int nv, const void *q, float *o,
     a.n_units = wk.n_units;
     a.L = c->L;
     a.scale_log2 = c->scale * 1.4426950408889634f;
-    a.wide_waves = dense_wide_waves(wk.tiles, c->n_cu);
+    a.wide_waves = wk.wide_waves;
     const DenseRole role = (int)l.g_heads.size() == H ? DenseRole::kFullWindow
                            : (c->cfg.spatial_cell > 0 || c->cfg.sd_blocks == 2)
                                ? DenseRole::kVariant
@@ -803,10 +823,11 @@ hc_status hc_attention(hc_ctx *c, int layer, const void *q, const uint8_t *head_
   if ((st = ensure_plan(c, l, nv)) != HC_OK) return st;
   if ((st = need_part(c, l.plan_slots)) != HC_OK) return st;
   if ((st = need_sp_part(c, sp_split_rows(c, l))) != HC_OK) return st;
+  const int D = c->cfg.head_dim;
   LayerWork wk;
   wk.units = l.units;
   wk.n_units = l.n_units;
-  wk.tiles = l.plan_tiles;
+  wk.wide_waves = D == 128 && dense_wide_waves(l.plan_tiles, c->n_cu);
   wk.comb = l.comb;
   wk.n_comb = l.n_comb;
   wk.part = (float *)c->part.p;
@@ -839,35 +860,22 @@ hc_status hc_attention_static(hc_ctx *c, int layer, const void *q, const uint8_t
   // partials and their (max, sum) pairs, each 256-byte aligned.  Where not all of
   // them fit, the Spatial partials are merged before the dense units run, in the
   // place that the dense ones then take.
-  auto al = [](size_t b) { return (b + 255) / 256 * 256; };
-  auto lists = [&] {
-    return al((size_t)static_n_units(p) * sizeof(DenseUnit)) +
-           al((size_t)static_n_comb(p) * sizeof(CombineItem));
-  };
-  const size_t slot_bytes = (size_t)partial_floats(D) * sizeof(float);
-  const size_t need = lists() + al((size_t)static_n_slots(p) * slot_bytes);
+  const size_t need = static_dense_bytes(p);
   if (need > kStaticScratchBytes)
     return fail(c, HC_E_INVAL, "hc_attention_static: layer %d needs %zu bytes of scratch, the "
                 "static buffer holds %zu", layer, need, (size_t)kStaticScratchBytes);
   if (l.static_nv != nv) {
-    // room for the longest list (32 ranges) is left out of the slots
-    const size_t longest = al(((size_t)p.n_g * kMaxSrcBlocks + (size_t)p.n_sd * 2) * p.nqt *
-                              sizeof(DenseUnit)) +
-                           al(((size_t)p.n_g + p.n_sd) * p.nqt * sizeof(CombineItem));
-    const int64_t max_slots =
-        longest + 256 < kStaticScratchBytes ? (kStaticScratchBytes - longest - 256) / slot_bytes : 0;
-    l.static_parts = static_global_parts(p, c->n_cu, dense_groups_per_cu(D), max_slots,
-                                          merged_anyway(c, l, nv));
+    l.chosen = static_choice_shared(c, p, merged_anyway(c, l, nv));
     l.static_nv = nv;
   }
-  p.g_parts = l.static_parts;
+  p.g_parts = l.chosen.parts;
   const size_t n_units = (size_t)static_n_units(p), n_comb = (size_t)static_n_comb(p);
-  const size_t b_units = al(n_units * sizeof(DenseUnit)), b_lists = lists();
+  const size_t b_units = align256(n_units * sizeof(DenseUnit)), b_lists = static_list_bytes(p);
   const int n_sp = (int)l.sp_heads.size();
   int split = std::min(l.sp_split, nv * F);
   auto sp_rows = [&](int sp) { return sp > 1 ? (size_t)sp * n_sp * c->L : 0; };
-  auto sp_bytes = [&](int sp) { return al(sp_rows(sp) * D * sizeof(float)) + sp_rows(sp) * 2 * sizeof(float); };
-  size_t sp_at = b_lists + al((size_t)static_n_slots(p) * slot_bytes);
+  auto sp_bytes = [&](int sp) { return align256(sp_rows(sp) * D * sizeof(float)) + sp_rows(sp) * 2 * sizeof(float); };
+  size_t sp_at = static_dense_bytes(p);
   const bool shared = sp_at + sp_bytes(split) > kStaticScratchBytes;
   if (shared) {
     sp_at = b_lists;
@@ -879,14 +887,13 @@ hc_status hc_attention_static(hc_ctx *c, int layer, const void *q, const uint8_t
   LayerWork wk;
   wk.units = (const DenseUnit *)base;
   wk.n_units = (int)n_units;
-  wk.tiles = (p.n_g * (round_up_tiles((int64_t)nv * c->L) / kKTile) +
-              (int64_t)p.n_sd * p.sd_parts * (round_up_tiles(c->L) / kKTile)) * p.nqt;
+  wk.wide_waves = l.chosen.wide;
   wk.comb = (const CombineItem *)(base + b_units);
   wk.n_comb = (int)n_comb;
   wk.part = (float *)(base + b_lists);
   wk.sp_split = split;
   wk.sp_part = (float *)(base + sp_at);
-  wk.sp_ml = (float *)(base + sp_at + al(sp_rows(split) * D * sizeof(float)));
+  wk.sp_ml = (float *)(base + sp_at + align256(sp_rows(split) * D * sizeof(float)));
   wk.shared_part = shared;
   HC_HIP(c, launch_static_plan(p, (DenseUnit *)wk.units, (CombineItem *)wk.comb, s));
   return run_layer(c, l, nv, q, o, wk, s);

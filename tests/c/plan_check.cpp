@@ -3,6 +3,8 @@
 // the runtime's (Global heads: one unit per window block and 128-query tile,
 // merged per tile; Sink/Dummy heads: one unit per tile writing o; cells:
 // query-mapped units) for several layer mixes and device sizes.
+#include <chrono>
+#include <cmath>
 #include <cstdio>
 #include <cstdlib>
 #include <map>
@@ -287,7 +289,116 @@ static void static_plan_matches(int L, int nv, int sd_blocks, int n_g, int n_sd,
   }
 }
 
+// ---------------------------------------------------------------------------
+// The choice of key ranges and kernel for the device-built work list.
+// ---------------------------------------------------------------------------
+static StaticPlan static_plan(int d, int L, int nv, int n_sd, int n_g, int sd_blocks = 1) {
+  StaticPlan p{};
+  p.d = d; p.L = L; p.nv = nv; p.nqt = (L + kQTile - 1) / kQTile;
+  p.sd_parts = (sd_blocks == 2 && nv >= 2) ? 2 : 1;
+  p.n_g = n_g; p.n_sd = n_sd;
+  return p;
+}
+
+// The groups of slots end as a heap of single slots does.
+static void slot_groups_match() {
+  unsigned seed = 1;
+  auto rnd = [&](int n) { seed = seed * 1664525u + 1013904223u; return (int)((seed >> 8) % n); };
+  for (int rep = 0; rep < 300; ++rep) {
+    const int slots = 1 + rnd(96);
+    SlotGroups g(slots);
+    std::vector<double> cost;
+    for (int b = 1 + rnd(9); b > 0; --b) {
+      const double c = 1 + rnd(40) + 0.5 * rnd(2);
+      const int n = 1 + rnd(200);
+      g.add(c, n);
+      cost.insert(cost.end(), n, c);
+      CHECK(g.end == plan_detail::run_makespan(cost, slots), "%d slots: %f", slots, g.end);
+    }
+    int held = 0;
+    for (int i = 0; i < g.groups; ++i) held += g.n[i];
+    CHECK(held == slots, "%d of %d slots", held, slots);
+  }
+  // ... and a list is run by run what its units are one by one
+  for (int n_g : {0, 1, 3})
+    for (int parts : {1, 3, 7, 11}) {
+      StaticPlan p = static_plan(128, 1320, 7, 5, n_g);
+      p.g_parts = parts;
+      const double all = static_dense_us(p, kCost128, 256);
+      const double each = dense_us(kCost128, static_n_units(p), 256, [&](int i, int *same) {
+        *same = 1;
+        return plan_detail::unit_tiles(static_dense_unit(p, i));
+      });
+      CHECK(std::abs(all - each) < 1e-9, "%d Global heads, %d ranges: %f and %f us", n_g, parts, all, each);
+    }
+}
+
+static void static_choices() {
+  const size_t scratch = (size_t)64 << 20;
+  int n = 0, cut = 0;
+  for (int d : {64, 128})
+    for (int L : {8, 96, 440, 792, 1320, 2760, 4680, 10800, 24480})
+      for (int nv : {1, 2, 3, 5, 7, 8, 32})
+        for (auto h : std::vector<std::pair<int, int>>{{1, 0}, {0, 12}, {2, 2}, {4, 8}, {12, 0}, {3, 7}, {16, 0}, {64, 0}})
+          for (int more = 0; more < 3; ++more) {   // 1: split Spatial heads, 2: two-block heads
+            StaticPlan p = static_plan(d, L, nv, h.second, h.first, more == 2 ? 2 : 1);
+            if (static_dense_bytes(p) > scratch) continue;   // refused before a choice is made
+            const bool merged = more == 1 || (p.sd_parts == 2 && p.n_sd > 0);
+            const StaticChoice c = static_choice(p, 256, static_max_slots(p, scratch), merged);
+            const int64_t tiles = ((int64_t)nv * L + kKTile - 1) / kKTile;
+            CHECK(c.parts == nv || (c.parts >= 1 && c.parts <= std::min<int64_t>(tiles, kMaxSrcBlocks)),
+                  "d %d L %d nv %d heads %d/%d: %d ranges", d, L, nv, h.first, h.second, c.parts);
+            CHECK(d == 128 || !c.wide, "64 queries per wave for 64-dim heads");
+            p.g_parts = c.parts;
+            CHECK(static_dense_bytes(p) <= scratch, "d %d L %d nv %d heads %d/%d, %d ranges: %zu bytes", d, L, nv,
+                  h.first, h.second, c.parts, static_dense_bytes(p));
+            ++n;
+            cut += c.parts != nv;
+          }
+  std::printf("plan_check: %d range choices fit the scratch, %d other than one per block\n", n, cut);
+  // choices whose alternatives were measured (us: the choice, and what it must not be)
+  struct { int d, L, nv, n_sd, n_g; bool merged; int parts; bool wide; } known[] = {
+      {128, 4680, 7, 7, 3, true, 6, true},    // 334; one per block 373
+      {128, 4680, 7, 10, 2, false, 7, true},  // 248; 32 queries per wave 265
+      {128, 4680, 7, 11, 1, false, 7, false},
+      {128, 4680, 7, 0, 3, false, 4, true},   // 212; one per block 235
+      {128, 6912, 4, 9, 3, false, 4, false},  // 469; three ranges, 64 queries per wave 473
+      {128, 10800, 5, 10, 2, false, 5, false},// 1049; 64 queries per wave 1070
+      {128, 4680, 2, 8, 4, false, 2, false},  // 203; 64 queries per wave 231
+      {128, 4680, 3, 8, 4, false, 3, false},  // 215; 64 queries per wave 233
+      {128, 10800, 1, 10, 2, false, 1, true}, // 570; 32 queries per wave 607
+      {128, 792, 1, 0, 12, false, 1, false},  // 26; three ranges 33
+      {128, 640, 4, 0, 12, false, 4, false},  // 34; two ranges 40
+      {128, 2760, 5, 4, 4, false, 4, false},  // 108; one per block 131
+      {64, 440, 7, 0, 16, false, 4, false},   // 28; two ranges 31
+      {64, 640, 4, 0, 12, false, 4, false},   // 26; two ranges 28
+      {64, 792, 1, 0, 12, false, 1, false},   // 22; two ranges 26
+      {64, 4680, 7, 10, 2, false, 7, false},  // 160; five ranges 169
+      {64, 4680, 7, 7, 3, true, 6, false}};   // 212; one per block 221
+  for (auto &k : known) {
+    const StaticPlan p = static_plan(k.d, k.L, k.nv, k.n_sd, k.n_g);
+    const StaticChoice c = static_choice(p, 256, static_max_slots(p, scratch), k.merged);
+    CHECK(c.parts == k.parts && c.wide == k.wide, "d %d L %d nv %d heads %d/%d: %d ranges, %s", k.d, k.L, k.nv, k.n_g,
+          k.n_sd, c.parts, c.wide ? "wide" : "not wide");
+  }
+  // the choice is made inside a call of 30 us and more: with these checks built in it
+  // takes some 0.2 ms where simulating unit by unit took 5
+  for (auto &k : known) {
+    const StaticPlan p = static_plan(k.d, k.L, k.nv, k.n_sd, k.n_g);
+    double best = 1e30;
+    for (int rep = 0; rep < 5; ++rep) {
+      const auto t0 = std::chrono::steady_clock::now();
+      static_choice(p, 256, static_max_slots(p, scratch), k.merged);
+      best = std::min(best, std::chrono::duration<double, std::micro>(std::chrono::steady_clock::now() - t0).count());
+    }
+    std::printf("plan_check: choice d %d L %d nv %d heads %d/%d: %.0f us\n", k.d, k.L, k.nv, k.n_g, k.n_sd, best);
+    CHECK(best < 1000, "%.0f us for one choice", best);
+  }
+}
+
 int main() {
+  slot_groups_match();
+  static_choices();
   // the device-built work list of the no-allocation entry point
   for (int L : {8, 72, 128, 384, 4680})
     for (int nv = 1; nv <= 7; ++nv)

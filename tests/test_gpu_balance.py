@@ -77,7 +77,8 @@ def test_uncut_small_windows(hc, d, L, nv):
 @pytest.mark.parametrize("types", [(3, 3, 3, 0, 0, 1, 1, 0, 1, 1, 2, 2), (3, 3, 1, 2), (3, 0)])
 def test_static_key_ranges_480p(hc, types):
     """The no-allocation call cuts Global windows into as many ranges as end first, not
-    at block borders, and its Spatial partials reuse the merged dense partials' place."""
+    at block borders (six for the first table), and its dense partials take the place of
+    the Spatial ones, which are merged by then."""
     import torch
     types = np.array(types, np.uint8)
     w = S.Workload("ranges", 1, len(types), 128, 30, 52, 3, 7, 4, 2, 484, (0, 0, 0, len(types)))
