@@ -39,7 +39,11 @@
  *    graph.  The context's host state (current block, window fill) changes when
  *    a call is made, not when a graph replays it, so a captured sequence must not
  *    advance the block; the first hc_attention at a new window fill builds the
- *    layer's work list (it allocates and synchronises) and runs eagerly.
+ *    layer's work list (it allocates, and waits for the device where an older list
+ *    may be in use or the layer's cache was last written on another stream) and
+ *    runs eagerly.  Partial results are shared by a context's layers: a call that
+ *    sets a table or builds a list may move them, so a graph is captured after the
+ *    last such call of any layer and replayed until the next.
  *  * Errors: every entry point returns an hc_status; nothing is thrown across
  *    the ABI.  On failure the context keeps a message (hc_last_error) and the
  *    layer state is left as it was before the call, with two exceptions: after

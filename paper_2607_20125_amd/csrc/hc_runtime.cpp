@@ -43,6 +43,8 @@ struct Layer {
   int64_t plan_tiles = 0;      // key tiles of all units
   int64_t plan_slots = 0;      // partial slots that the units write
   int plan_nv = -1;            // valid window blocks the plan was built for
+  bool plan_used = false;      // launches may still read the plan's memory
+  hipStream_t kv_stream = nullptr;   // the stream that last wrote the compact buffers
   int static_nv = -1;          // window fill that `chosen` is for
   StaticChoice chosen{};       // the device-built work list
   int sp_split = 1;            // key-frame split of the Spatial work (full window)
@@ -161,6 +163,7 @@ void free_layer(Layer &l) {
   free_buf(l.plan);
   l.k_sd = l.v_sd = l.k_g = l.v_g = l.k_sp = l.v_sp = DevBuf{};
   drop_plan(l);
+  l.plan_used = false;
 }
 
 // --- profiling ----------------------------------------------------------------
@@ -301,6 +304,8 @@ hc_status install_types(hc_ctx *c, Layer &l, const uint8_t *types, hipStream_t s
     free_buf(l.kv);
     if ((st = dev_malloc(c, l.kv, total)) != HC_OK) return st;
   }
+  l.plan_used = false;
+  l.kv_stream = s;
   HC_HIP(c, hipMemsetAsync(l.kv.p, 0, total, s));
   unsigned char *at = (unsigned char *)l.kv.p;
   for (DevBuf *b : {&l.k_sd, &l.v_sd, &l.k_g, &l.v_g, &l.k_sp, &l.v_sp}) {
@@ -366,7 +371,7 @@ hc_status upload(hc_ctx *c, DevBuf &b, const std::vector<T> &v) {
   return HC_OK;
 }
 
-hc_status ensure_plan(hc_ctx *c, Layer &l, int nv) {
+hc_status ensure_plan(hc_ctx *c, Layer &l, int nv, hipStream_t s) {
   if (l.plan_nv == nv) return HC_OK;
   std::vector<DenseUnit> units;
   std::vector<CombineItem> comb;
@@ -388,12 +393,16 @@ hc_status ensure_plan(hc_ctx *c, Layer &l, int nv) {
                   (long long)unit_region_keys(u, regions, D));
     }
   }
-  // launches of the previous plan are over before its memory is written again, and
-  // so is the split or append that this window fill comes from, on whatever stream
-  if (!units.empty()) HC_HIP(c, hipDeviceSynchronize());
+  // launches of the previous plan are over before its memory is written again, and so
+  // is a split or append of this window fill on another stream than the caller's
+  // (hipStreamPerThread is another stream in every thread).  Not asked on the same
+  // stream: 8 us of the smallest layer's first call.
+  if (l.plan_used || (!units.empty() && (l.kv_stream != s || s == hipStreamPerThread)))
+    HC_HIP(c, hipDeviceSynchronize());
   // no plan until this one is complete: a failure below leaves a rebuild for
   // the next call instead of a list that does not match its counts
   drop_plan(l);
+  l.plan_used = false;
   hc_status st;
   int64_t slots = 0;
   for (const CombineItem &it : comb) slots = std::max<int64_t>(slots, (int64_t)it.slot0 + it.n_slots);
@@ -419,6 +428,7 @@ hc_status ensure_plan(hc_ctx *c, Layer &l, int nv) {
   for (const DenseUnit &u : units) l.plan_tiles += plan_detail::unit_tiles(u);
   l.plan_slots = slots;
   l.plan_nv = nv;
+  l.plan_used = true;
   return HC_OK;
 }
 
@@ -807,6 +817,7 @@ hc_status hc_append_block(hc_ctx *c, int layer, int64_t block, const void *k_blk
   a.sink_slot[0] = (int8_t)sd_slot(c, HC_SINK, block, block);
   a.dummy_slot[0] = (int8_t)sd_slot(c, HC_DUMMY, block, block);
   hipStream_t s = (hipStream_t)stream;
+  l.kv_stream = s;
   st = timed_launch(c, s, HC_K_SCATTER, [&] { return launch_scatter(a, c->cfg.n_heads, s); });
   if (st != HC_OK) return st;
   l.cur_block = block;
@@ -820,7 +831,7 @@ hc_status hc_attention(hc_ctx *c, int layer, const void *q, const uint8_t *head_
   Layer &l = c->layers[layer];
   HC_HIP(c, hipSetDevice(c->device));
   const int nv = n_valid_blocks(c, l.cur_block);
-  if ((st = ensure_plan(c, l, nv)) != HC_OK) return st;
+  if ((st = ensure_plan(c, l, nv, (hipStream_t)stream)) != HC_OK) return st;
   if ((st = need_part(c, l.plan_slots)) != HC_OK) return st;
   if ((st = need_sp_part(c, sp_split_rows(c, l))) != HC_OK) return st;
   const int D = c->cfg.head_dim;
@@ -1086,7 +1097,7 @@ hc_status hc_classify_heads(hc_ctx *c, int layer, int64_t cur_block, const void 
   if (st != HC_OK) return st;
   // the routed work list is built while the split runs (without memory for it, that
   // is left to the layer's first hc_attention)
-  st = ensure_plan(c, c->layers[layer], W);
+  st = ensure_plan(c, c->layers[layer], W, s);
   if (st == HC_E_NOMEM) c->err.clear();
   else if (st != HC_OK) return st;
   HC_HIP(c, hipStreamSynchronize(s));

@@ -127,13 +127,23 @@ void shared_buffers_after_failed_growth() {
   }
 }
 
-// The first hc_attention at a window fill synchronises: a table set on one stream is
-// attended from another.  Memory that a call clears is clear before the caller's
+// A table set, or a block appended, on one stream is attended for the first time from
+// another; on the same stream nothing is waited for.  Memory that a call clears is clear before the caller's
 // stream uses it.
 void first_attention_on_another_stream() {
   for (const auto &t : {kFew, kMany}) {
     Ctx x(config(1, 4));
     CHECK(x.set(0, t, kA) == HC_OK && x.attend(0, t, kB) == HC_OK, "%s", hc_last_error(x.c));
+    (void)hipDeviceSynchronize();
+    CHECK(x.set(0, t, kA) == HC_OK, "%s", hc_last_error(x.c));
+    (void)hipDeviceSynchronize();
+    CHECK(x.append(0, kB) == HC_OK && x.attend(0, t, kA) == HC_OK, "%s", hc_last_error(x.c));
+    (void)hipDeviceSynchronize();
+    CHECK(x.set(0, t, kA) == HC_OK, "%s", hc_last_error(x.c));
+    const int syncs = fake::syncs;
+    CHECK(x.attend(0, t, kA) == HC_OK && fake::syncs == syncs, "%d waits", fake::syncs - syncs);
+    CHECK(x.set(0, t, hipStreamPerThread) == HC_OK && x.attend(0, t, hipStreamPerThread) == HC_OK, "per thread");
+    CHECK(fake::syncs > syncs + 1, "no wait on hipStreamPerThread");   // one for the kept buffers
     (void)hipDeviceSynchronize();
   }
   // (a layer without dense work has no list to build: its first call only launches)
