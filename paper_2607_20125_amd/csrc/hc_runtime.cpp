@@ -140,14 +140,15 @@ void free_buf(DevBuf &b) {
   b = DevBuf{};
 }
 
-hc_status alloc_zero(hc_ctx *c, DevBuf &b, size_t bytes) {
+// Memory cleared on `s`, the stream that uses it next.
+hc_status alloc_zero(hc_ctx *c, DevBuf &b, size_t bytes, hipStream_t s) {
   free_buf(b);
   if (bytes == 0) return HC_OK;
   hc_status st = dev_malloc(c, b, bytes);
   if (st != HC_OK) return st;
-  HC_HIP(c, hipMemset(b.p, 0, bytes));
-  // waited for: the caller's stream need not be ordered after the null stream
-  HC_HIP(c, hipStreamSynchronize(nullptr));
+  const hipError_t cleared = hipMemsetAsync(b.p, 0, bytes, s);
+  if (cleared != hipSuccess) free_buf(b);      // not kept as if it were clear
+  HC_HIP(c, cleared);
   return HC_OK;
 }
 
@@ -244,23 +245,27 @@ uint16_t *sp_frames(const hc_ctx *c, const DevBuf &b) {
 // least `rows` rows of Spatial splits.  The old memory is released before the new is
 // allocated, so while that fails there is none: the counts say so, and the next
 // hc_attention of any layer asks again.
-hc_status need_part(hc_ctx *c, int64_t slots) {
+hc_status need_part(hc_ctx *c, int64_t slots, hipStream_t s) {
   if (slots <= c->part_slots) return HC_OK;
   HC_HIP(c, hipDeviceSynchronize());
   c->part_slots = 0;
-  hc_status st = alloc_zero(c, c->part, (size_t)slots * partial_floats(c->cfg.head_dim) * 4);
-  if (st == HC_OK) c->part_slots = slots;
-  return st;
+  hc_status st = alloc_zero(c, c->part, (size_t)slots * partial_floats(c->cfg.head_dim) * 4, s);
+  if (st != HC_OK) return st;
+  HC_HIP(c, hipStreamSynchronize(s));      // the next layer to use it may be on another stream
+  c->part_slots = slots;
+  return HC_OK;
 }
 
-hc_status need_sp_part(hc_ctx *c, int64_t rows) {
+hc_status need_sp_part(hc_ctx *c, int64_t rows, hipStream_t s) {
   if (rows <= c->sp_part_rows) return HC_OK;
   HC_HIP(c, hipDeviceSynchronize());
   c->sp_part_rows = 0;
-  hc_status st = alloc_zero(c, c->sp_part, (size_t)rows * c->cfg.head_dim * 4);
-  if (st == HC_OK) st = alloc_zero(c, c->sp_ml, (size_t)rows * 2 * 4);
-  if (st == HC_OK) c->sp_part_rows = rows;
-  return st;
+  hc_status st = alloc_zero(c, c->sp_part, (size_t)rows * c->cfg.head_dim * 4, s);
+  if (st == HC_OK) st = alloc_zero(c, c->sp_ml, (size_t)rows * 2 * 4, s);
+  if (st != HC_OK) return st;
+  HC_HIP(c, hipStreamSynchronize(s));
+  c->sp_part_rows = rows;
+  return HC_OK;
 }
 
 int64_t sp_split_rows(const hc_ctx *c, const Layer &l) {
@@ -316,12 +321,12 @@ hc_status install_types(hc_ctx *c, Layer &l, const uint8_t *types, hipStream_t s
   // Spatial work split over key frames when the layer has few Spatial heads
   l.sp_split = c->cfg.spatial_cell > 0 ? 1
                                          : spatial_split(c, (int)l.sp_heads.size(), c->cfg.spatial_radius);
-  if ((st = need_sp_part(c, sp_split_rows(c, l))) != HC_OK) return st;
+  if ((st = need_sp_part(c, sp_split_rows(c, l), s)) != HC_OK) return st;
   // partial slots for the largest plan of this layer (full window)
   const int64_t nqt = (c->L + kQTile - 1) / kQTile;
   const int64_t need = ((int64_t)l.g_heads.size() * c->cfg.window_blocks +
                         (int64_t)l.sd_heads.size() * (c->cfg.sd_blocks == 2 ? 2 : 0)) * nqt;
-  if ((st = need_part(c, need)) != HC_OK) return st;
+  if ((st = need_part(c, need, s)) != HC_OK) return st;
   l.has_types = true;
   return HC_OK;
 }
@@ -365,7 +370,7 @@ template <class T>
 hc_status upload(hc_ctx *c, DevBuf &b, const std::vector<T> &v) {
   free_buf(b);
   if (v.empty()) return HC_OK;
-  hc_status st = alloc_zero(c, b, v.size() * sizeof(T));
+  hc_status st = dev_malloc(c, b, v.size() * sizeof(T));
   if (st != HC_OK) return st;
   HC_HIP(c, hipMemcpy(b.p, v.data(), v.size() * sizeof(T), hipMemcpyHostToDevice));
   return HC_OK;
@@ -406,7 +411,7 @@ hc_status ensure_plan(hc_ctx *c, Layer &l, int nv, hipStream_t s) {
   hc_status st;
   int64_t slots = 0;
   for (const CombineItem &it : comb) slots = std::max<int64_t>(slots, (int64_t)it.slot0 + it.n_slots);
-  if ((st = need_part(c, slots)) != HC_OK) return st;
+  if ((st = need_part(c, slots, s)) != HC_OK) return st;
   // both lists in one copy
   const size_t b_units = (units.size() * sizeof(DenseUnit) + 255) / 256 * 256;
   std::vector<unsigned char> both(b_units + comb.size() * sizeof(CombineItem));
@@ -832,8 +837,8 @@ hc_status hc_attention(hc_ctx *c, int layer, const void *q, const uint8_t *head_
   HC_HIP(c, hipSetDevice(c->device));
   const int nv = n_valid_blocks(c, l.cur_block);
   if ((st = ensure_plan(c, l, nv, (hipStream_t)stream)) != HC_OK) return st;
-  if ((st = need_part(c, l.plan_slots)) != HC_OK) return st;
-  if ((st = need_sp_part(c, sp_split_rows(c, l))) != HC_OK) return st;
+  if ((st = need_part(c, l.plan_slots, (hipStream_t)stream)) != HC_OK) return st;
+  if ((st = need_sp_part(c, sp_split_rows(c, l), (hipStream_t)stream)) != HC_OK) return st;
   const int D = c->cfg.head_dim;
   LayerWork wk;
   wk.units = l.units;
@@ -915,10 +920,10 @@ namespace {
 // A classification buffer of at least `bytes`, kept by the context: allocated
 // and zeroed the first time, reused as is afterwards.  Padding keys of the
 // window copies stay zero because later calls only rewrite real keys.
-hc_status keep(hc_ctx *c, DevBuf &b, size_t bytes) {
+hc_status keep(hc_ctx *c, DevBuf &b, size_t bytes, hipStream_t s) {
   if (b.p && b.bytes >= bytes) return HC_OK;
   HC_HIP(c, hipDeviceSynchronize());
-  return alloc_zero(c, b, bytes);
+  return alloc_zero(c, b, bytes, s);
 }
 
 // Eq. 5 on one head's statistics (HC_STAT_* order, float64): the first of Sink,
@@ -963,7 +968,7 @@ hc_status hc_classify_heads(hc_ctx *c, int layer, int64_t cur_block, const void 
   const int64_t tkeys = global_buffer_keys(W, L);
   const int64_t lead = c->geo.lead;
   const size_t tbytes = ((size_t)H * tkeys + 2 * lead) * D * 2;
-  if ((st = keep(c, c->cls_k, tbytes)) != HC_OK || (st = keep(c, c->cls_v, tbytes)) != HC_OK)
+  if ((st = keep(c, c->cls_k, tbytes, s)) != HC_OK || (st = keep(c, c->cls_v, tbytes, s)) != HC_OK)
     return st;
   uint16_t *tk = (uint16_t *)c->cls_k.p + lead * D, *tv = (uint16_t *)c->cls_v.p + lead * D;
   auto copy_window = [&](uint8_t kind, uint16_t *k, uint16_t *v, int64_t keys) {
@@ -983,7 +988,7 @@ hc_status hc_classify_heads(hc_ctx *c, int layer, int64_t cur_block, const void 
   int64_t sp_stride = tkeys * D;
   if (c->geo.pitch != c->cfg.grid_w) {
     const size_t pbytes = ((size_t)H * c->sp_keys + 2 * lead) * D * 2;
-    if ((st = keep(c, c->cls_pk, pbytes)) != HC_OK || (st = keep(c, c->cls_pv, pbytes)) != HC_OK)
+    if ((st = keep(c, c->cls_pk, pbytes, s)) != HC_OK || (st = keep(c, c->cls_pv, pbytes, s)) != HC_OK)
       return st;
     uint16_t *pk = (uint16_t *)c->cls_pk.p + lead * D, *pv = (uint16_t *)c->cls_pv.p + lead * D;
     if ((st = copy_window(HC_SPATIAL, pk, pv, c->sp_keys)) != HC_OK) return st;
@@ -993,7 +998,7 @@ hc_status hc_classify_heads(hc_ctx *c, int layer, int64_t cur_block, const void 
   // 2. O_ref, O_sink, O_dummy (Eq. 2 and the temporal proxies) in one sweep, O_spatial (r_p)
   const size_t obytes = (size_t)H * L * D * 4;
   for (int i = 0; i < 4; ++i)
-    if ((st = keep(c, c->cls_o[i], obytes)) != HC_OK) return st;
+    if ((st = keep(c, c->cls_o[i], obytes, s)) != HC_OK) return st;
   float *o_ref = (float *)c->cls_o[0].p, *o_sink = (float *)c->cls_o[1].p;
   float *o_dum = (float *)c->cls_o[2].p, *o_sp = (float *)c->cls_o[3].p;
   {
@@ -1002,7 +1007,7 @@ hc_status hc_classify_heads(hc_ctx *c, int layer, int64_t cur_block, const void 
     // temporal proxies are the partials of block 0 (O_sink) and of the
     // current block (O_dummy) normalised on their own, so their keys are not
     // read a second time.
-    if ((st = keep(c, c->cls_part, (size_t)H * nqt * W * partial_floats(D) * 4)) != HC_OK)
+    if ((st = keep(c, c->cls_part, (size_t)H * nqt * W * partial_floats(D) * 4, s)) != HC_OK)
       return st;
     float *part = (float *)c->cls_part.p;
     // the work lists depend on the configuration only: built and uploaded once
@@ -1016,13 +1021,8 @@ hc_status hc_classify_heads(hc_ctx *c, int layer, int64_t cur_block, const void 
       const std::vector<KeyRegion> regions = {{tk, (int64_t)H, tkeys}};
       if (first_unit_outside(units, regions, D) >= 0)
         return fail(c, HC_E_STATE, "internal: a classification unit reads past its head");
-      if ((st = keep(c, c->cls_units, units.size() * sizeof(DenseUnit))) != HC_OK ||
-          (st = keep(c, c->cls_comb, comb.size() * sizeof(CombineItem))) != HC_OK)
+      if ((st = upload(c, c->cls_units, units)) != HC_OK || (st = upload(c, c->cls_comb, comb)) != HC_OK)
         return st;
-      HC_HIP(c, hipMemcpy(c->cls_units.p, units.data(), units.size() * sizeof(DenseUnit),
-                          hipMemcpyHostToDevice));
-      HC_HIP(c, hipMemcpy(c->cls_comb.p, comb.data(), comb.size() * sizeof(CombineItem),
-                          hipMemcpyHostToDevice));
       c->cls_n_units = (int)units.size();
       c->cls_n_comb = (int)comb.size();
     }
@@ -1065,7 +1065,7 @@ hc_status hc_classify_heads(hc_ctx *c, int layer, int64_t cur_block, const void 
   // 3. per-token and then per-head statistics on the device (float64), the
   // decision on the host
   const int groups = cls_stat_groups(L);
-  if ((st = keep(c, c->cls_tok, (size_t)H * (L + groups * 4 + HC_N_STATS) * sizeof(double))) != HC_OK)
+  if ((st = keep(c, c->cls_tok, (size_t)H * (L + groups * 4 + HC_N_STATS) * sizeof(double), s)) != HC_OK)
     return st;
   double *cos_sp = (double *)c->cls_tok.p;
   double *sums = cos_sp + (size_t)H * L;
