@@ -17,6 +17,9 @@ namespace hc {
 
 inline int64_t round_up_tiles(int64_t keys) { return (keys + kKTile - 1) / kKTile * kKTile; }
 
+// key tiles of a unit (0: padding)
+inline int unit_tiles(const DenseUnit &u) { return (u.kv1 - u.kv0 + kKTile - 1) / kKTile; }
+
 // ---------------------------------------------------------------------------
 // Keys per head of the buffers the dense kernel reads.  A unit's DMA moves
 // whole kKTile-key tiles from kv0, so it reads up to kKTile - 1 keys past kv1:
@@ -363,8 +366,6 @@ constexpr double kUnitOverheadTiles = 4.0;   // fixed cost of a unit (Q load, fi
 constexpr int kMinPieceTiles = 12;
 constexpr int kMaxPieces = 8;
 
-inline int unit_tiles(const DenseUnit &u) { return (u.kv1 - u.kv0 + kKTile - 1) / kKTile; }
-
 // End time of a whole run, by the standard library's heap (the CPU checks hold
 // the plans against it).
 inline double run_makespan(const std::vector<double> &cost, int slots) {
@@ -570,8 +571,8 @@ struct DenseCost {
   double lone;
 };
 inline constexpr DenseCost kCost64 = {0.369, 4.0, 0.2};
-inline constexpr DenseCost kCost128 = {0.619, 2.0, 0.2};        // 32 queries per wave
-inline constexpr DenseCost kCostWide128 = {0.564, 4.0, 1.0};    // 64 queries per wave
+inline constexpr DenseCost kCost128 = {0.619, 2.0, 0.3};        // 32 queries per wave
+inline constexpr DenseCost kCostWide128 = {0.564, 5.0, 1.0};    // 64 queries per wave
 
 // A merge launch, and one slot's way through memory (33 and 66 KB), in us.
 inline constexpr double merge_launch_us(int d) { return d == 64 ? 4.0 : 5.3; }
@@ -614,8 +615,9 @@ struct SlotGroups {
   }
 };
 
-// Time of a launch of n_units units in list order.  tiles(i, &same): the key tiles of
-// unit i (0: padding) and how many units from i on have as many.
+// Time of a launch of n_units units in list order.  tiles(i, e, &same): the key tiles
+// of unit i (0: padding) and how many units from i on have as many, counted as far as
+// e at least.
 template <class Tiles>
 inline double dense_us(const DenseCost &c, int n_units, int n_cu, Tiles &&tiles) {
   const int cus = n_cu / 8, per = n_units / 8, rem = n_units % 8;
@@ -625,7 +627,7 @@ inline double dense_us(const DenseCost &c, int n_units, int n_cu, Tiles &&tiles)
     SlotGroups g1(cus), g2(2 * cus);
     bool alike = true;
     for (int i = b, same = 0; i < e; i += same) {
-      const int nt = tiles(i, &same);
+      const int nt = tiles(i, e, &same);
       alike = alike && i == b && same >= n_units - b;
       same = std::min(same, e - i);
       if (nt == 0) continue;
@@ -644,6 +646,40 @@ inline bool dense_us_covers(int n_cu) {
   return n_cu > 0 && n_cu % 8 == 0 && n_cu / 4 <= SlotGroups::kMax;
 }
 
+// Whether a dense launch of 128-dim heads may run on waves of 64 queries, by its key
+// tiles (over all units): from 96 per resident work group (two per CU) on.  There the
+// estimate decides.  On a full GPU it is the faster kernel (less energy per product:
+// 115 tiles per group 0.95 of the time of 32-query waves, 16 heads, L = 4680; 600 and
+// more 0.93), but it has one wave per SIMD and two per work group, so a CU left with one
+// group uses half its SIMDs, and a unit's start and end weigh more: below the line 5
+// tiles per group took 1.27 (12 heads, L = 1320), 48 1.07 (4 Global heads, L = 2688, 7
+// blocks), 75 1.06 (2 Global heads, L = 4680); above it lists whose last rounds are not
+// full 1.03-1.19.
+inline bool dense_wide_waves(int64_t tiles, int n_cu) {
+  return tiles >= (int64_t)96 * dense_groups_per_cu(128) * n_cu;
+}
+
+// The same for a list as it is launched: 200 against 208 us for 8 Global heads of six
+// blocks of 2856 tokens, whose cut tails end unevenly.  Tail-balanced lists of 150 tiles
+// per group or more are not estimated (3-20 us): all 30 drawn ones ran in 0.94-1.00 of
+// the time.
+inline bool dense_wide_waves(const std::vector<DenseUnit> &units, int n_cu, bool balanced) {
+  int64_t tiles = 0;
+  for (const DenseUnit &u : units) tiles += unit_tiles(u);
+  if (!dense_wide_waves(tiles, n_cu)) return false;
+  if (!dense_us_covers(n_cu) || (balanced && tiles >= (int64_t)150 * dense_groups_per_cu(128) * n_cu))
+    return true;
+  auto tiles_of = [&](int i, int e, int *same) {
+    const int nt = unit_tiles(units[i]);
+    int j = i + 1;
+    while (j < e && unit_tiles(units[j]) == nt) ++j;
+    *same = j - i;
+    return nt;
+  };
+  return dense_us(kCostWide128, (int)units.size(), n_cu, tiles_of) <=
+         dense_us(kCost128, (int)units.size(), n_cu, tiles_of);
+}
+
 // The device-built work list of the no-allocation call: its key ranges per Global head
 // and the kernel it runs on.
 struct StaticChoice {
@@ -654,7 +690,7 @@ struct StaticChoice {
 inline double static_dense_us(const StaticPlan &p, const DenseCost &c, int n_cu) {
   const int gp = static_g_parts(p), ng = p.n_g * gp * p.nqt, n = static_n_units(p);
   const bool equal = gp == 1 || gp == p.nv;
-  return dense_us(c, n, n_cu, [&](int i, int *same) {
+  return dense_us(c, n, n_cu, [&](int i, int, int *same) {
     if (i >= ng) {
       *same = n - i;
       return (p.L + kKTile - 1) / kKTile;
@@ -674,14 +710,14 @@ inline double static_dense_us(const StaticPlan &p, const DenseCost &c, int n_cu)
 // 334 with 64 queries per wave), and so may waves of 32 queries (four Global and eight
 // Sink/Dummy heads of two 480P blocks: 203 against 231 us).  The estimate decides
 // both, with at most max_slots partial slots.  One range per block stays unless
-// another count is 2% faster, and 7% where that is fewer, longer ranges with 64
+// another count is 2% faster, and 9% where that is fewer, longer ranges with 64
 // queries per wave: those are estimated up to 6% too fast (6912 tokens, four blocks,
 // three ranges 473 us against 469).  15 us stand for the rest of the call.  Windows
 // that hc_attention leaves uncut are left uncut here.  Counts whose perfectly packed
 // list would not be faster are passed over unsimulated: 0-50 us a choice on one CPU
 // (30-420 us with every count simulated unit by unit).
 inline StaticChoice static_choice(StaticPlan p, int n_cu, int64_t max_slots, bool merged_anyway) {
-  constexpr double kGain = 0.02, kWideLongGain = 0.07, kRest = 15.0;
+  constexpr double kGain = 0.02, kWideLongGain = 0.09, kRest = 15.0;
   const int small = merged_anyway ? p.nv : global_parts(p.d, p.L, p.nv);
   const int64_t l_tiles = (p.L + kKTile - 1) / kKTile, w_tiles = ((int64_t)p.nv * p.L + kKTile - 1) / kKTile;
   const int64_t tiles = (p.n_g * w_tiles + (int64_t)p.n_sd * p.sd_parts * l_tiles) * p.nqt;

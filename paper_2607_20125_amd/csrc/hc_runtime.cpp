@@ -40,7 +40,7 @@ struct Layer {
   const DenseUnit *units = nullptr;
   const CombineItem *comb = nullptr;
   int n_units = 0, n_comb = 0;
-  int64_t plan_tiles = 0;      // key tiles of all units
+  bool plan_wide = false;      // 128-dim heads: the units run on waves of 64 queries
   int64_t plan_slots = 0;      // partial slots that the units write
   int plan_nv = -1;            // valid window blocks the plan was built for
   bool plan_used = false;      // launches may still read the plan's memory
@@ -83,6 +83,7 @@ struct hc_ctx {
   // four proxy outputs, the block partials, the work lists, the token statistics
   DevBuf cls_k, cls_v, cls_pk, cls_pv, cls_o[4], cls_part, cls_units, cls_comb, cls_tok;
   int cls_n_units = 0, cls_n_comb = 0;
+  bool cls_wide = false;       // 128-dim heads: the sweep runs on waves of 64 queries
   bool cls_done = false;       // cls_o holds the outputs of a successful classification
   void *scratch = nullptr;     // this device's fixed scratch (hc_attention_static)
   // the last choices of hc_attention_static: layers with as many heads of each kind
@@ -429,8 +430,7 @@ hc_status ensure_plan(hc_ctx *c, Layer &l, int nv, hipStream_t s) {
   l.comb = (const CombineItem *)((const unsigned char *)l.plan.p + b_units);
   l.n_units = (int)units.size();
   l.n_comb = (int)comb.size();
-  l.plan_tiles = 0;
-  for (const DenseUnit &u : units) l.plan_tiles += plan_detail::unit_tiles(u);
+  l.plan_wide = c->cfg.head_dim == 128 && dense_wide_waves(units, c->n_cu, true);
   l.plan_slots = slots;
   l.plan_nv = nv;
   l.plan_used = true;
@@ -839,11 +839,10 @@ hc_status hc_attention(hc_ctx *c, int layer, const void *q, const uint8_t *head_
   if ((st = ensure_plan(c, l, nv, (hipStream_t)stream)) != HC_OK) return st;
   if ((st = need_part(c, l.plan_slots, (hipStream_t)stream)) != HC_OK) return st;
   if ((st = need_sp_part(c, sp_split_rows(c, l), (hipStream_t)stream)) != HC_OK) return st;
-  const int D = c->cfg.head_dim;
   LayerWork wk;
   wk.units = l.units;
   wk.n_units = l.n_units;
-  wk.wide_waves = D == 128 && dense_wide_waves(l.plan_tiles, c->n_cu);
+  wk.wide_waves = l.plan_wide;
   wk.comb = l.comb;
   wk.n_comb = l.n_comb;
   wk.part = (float *)c->part.p;
@@ -1023,6 +1022,7 @@ hc_status hc_classify_heads(hc_ctx *c, int layer, int64_t cur_block, const void 
         return fail(c, HC_E_STATE, "internal: a classification unit reads past its head");
       if ((st = upload(c, c->cls_units, units)) != HC_OK || (st = upload(c, c->cls_comb, comb)) != HC_OK)
         return st;
+      c->cls_wide = D == 128 && dense_wide_waves(units, c->n_cu, false);
       c->cls_n_units = (int)units.size();
       c->cls_n_comb = (int)comb.size();
     }
@@ -1035,7 +1035,7 @@ hc_status hc_classify_heads(hc_ctx *c, int layer, int64_t cur_block, const void 
     a.n_units = c->cls_n_units;
     a.L = L;
     a.scale_log2 = c->scale * 1.4426950408889634f;
-    a.wide_waves = dense_wide_waves(c->cls_n_units * (round_up_tiles(L) / kKTile), c->n_cu);
+    a.wide_waves = c->cls_wide;
     st = timed_launch(c, s, HC_K_DENSE,
                       [&] { return launch_dense(a, D, DenseRole::kClassify, s); });
     if (st != HC_OK) return st;

@@ -22,18 +22,6 @@ constexpr int kKTile = 64;     // keys per dense KV tile
 // 64-dim heads need half the LDS and 168 registers, so three (four would need 128).
 inline constexpr int dense_groups_per_cu(int d) { return d == 64 ? 3 : 2; }
 
-// Which kernel a dense launch of 128-dim heads takes, by its key tiles (over all
-// units): the one of 64 queries per wave from 96 tiles per resident work group on.
-// It is faster on a full GPU (less energy per product), but has one wave per SIMD
-// and two per work group: a CU left with one work group, as in the last round of
-// a launch, uses half its SIMDs, and a unit's start and end weigh more.  Time
-// against waves of 32 queries: 5 tiles per group 1.27 (12 heads, L = 1320), 48
-// 1.07 (4 Global heads, L = 2688, 7 blocks), 75 1.06 (2 Global heads, L = 4680),
-// 115 0.95 (16 heads, L = 4680), 600 and more 0.93.
-inline bool dense_wide_waves(int64_t tiles, int n_cu) {
-  return tiles >= (int64_t)96 * dense_groups_per_cu(128) * n_cu;
-}
-
 // One dense work unit: kQTile queries of one head against the contiguous key range
 // [kv0, kv1) of a [keys][d] K buffer and its 8-key-grouped V buffer
 // ([keys/8][d][8]).  Every unit covers at most one window block of keys, so all

@@ -157,7 +157,7 @@ static void check_layer(const Layer &ly, int n_cu, bool expect_cut, int groups =
       const int b = x * p8 + std::min(x, r8), e = b + p8 + (x < r8 ? 1 : 0);
       std::vector<double> cost;
       for (int i = b; i < e; ++i)
-        if (us[i].head >= 0) cost.push_back(plan_detail::unit_tiles(us[i]) + plan_detail::kUnitOverheadTiles);
+        if (us[i].head >= 0) cost.push_back(unit_tiles(us[i]) + plan_detail::kUnitOverheadTiles);
       worst = std::max(worst, plan_detail::run_makespan(cost, slots));
     }
     return worst;
@@ -325,9 +325,9 @@ static void slot_groups_match() {
       StaticPlan p = static_plan(128, 1320, 7, 5, n_g);
       p.g_parts = parts;
       const double all = static_dense_us(p, kCost128, 256);
-      const double each = dense_us(kCost128, static_n_units(p), 256, [&](int i, int *same) {
+      const double each = dense_us(kCost128, static_n_units(p), 256, [&](int i, int, int *same) {
         *same = 1;
-        return plan_detail::unit_tiles(static_dense_unit(p, i));
+        return unit_tiles(static_dense_unit(p, i));
       });
       CHECK(std::abs(all - each) < 1e-9, "%d Global heads, %d ranges: %f and %f us", n_g, parts, all, each);
     }
@@ -396,7 +396,31 @@ static void static_choices() {
   }
 }
 
+// The kernel of a layer's own list: lists whose times on both kernels were measured.
+static void wide_lists() {
+  struct { int L, nv, n_sd, n_g; bool wide; } known[] = {
+      {2856, 6, 0, 8, false},    // 200; 64 queries per wave 208 us
+      {10800, 7, 6, 2, true},    // 0.93 of the time
+      {8640, 3, 3, 0, false},    // below 96 tiles per work group
+      {4680, 7, 0, 12, true}};
+  for (auto &k : known) {
+    const int D = 128;
+    std::vector<HeadKV> g, sd;
+    for (int i = 0; i < k.n_g; ++i) g.push_back(HeadKV{i, fake_base(0, i * D), fake_base(1, i * D)});
+    for (int i = 0; i < k.n_sd; ++i) sd.push_back(HeadKV{k.n_g + i, fake_base(2, i * D), fake_base(3, i * D)});
+    DensePlanShape shape;
+    shape.L = k.L; shape.nv = k.nv;
+    std::vector<DenseUnit> units;
+    std::vector<CombineItem> comb;
+    plan_dense_units(shape, g, sd, {}, 256, units, comb);
+    for (bool balanced : {true, false})          // (the estimate agrees where it is not asked)
+      CHECK(dense_wide_waves(units, 256, balanced) == k.wide, "L %d nv %d heads %d/%d: %s", k.L, k.nv, k.n_g,
+            k.n_sd, k.wide ? "not wide" : "wide");
+  }
+}
+
 int main() {
+  wide_lists();
   slot_groups_match();
   static_choices();
   // the device-built work list of the no-allocation entry point
