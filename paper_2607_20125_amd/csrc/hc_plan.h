@@ -81,6 +81,7 @@ struct HeadKV {
 };
 
 struct DensePlanShape {
+  int d = 128;               // head dimension
   int L = 0;                 // tokens per block
   int nv = 0;                // valid window blocks
   int g_parts = 0;           // key ranges per Global head (0: one per window block)
@@ -112,11 +113,23 @@ inline HC_HD void global_part(int L, int nv, int parts, int p, int32_t *kv0, int
 inline void balance_units(int n_cu, std::vector<DenseUnit> &units, std::vector<CombineItem> &comb,
                           int groups_per_cu = 2);
 
+// Work groups per CU that the balancing counts on.  128-dim heads: the two that are
+// resident.  The three of 64-dim heads share the CU's rate, one alone nearly reaching
+// it, so what ends a launch is the work per CU, not per group: with one slot per CU 90
+// drawn layers took 0.978 of the time with three (0.985 with two), and the layers of
+// two to three units per CU that three had made 4-5% slower than two are faster again
+// (7552 tokens, 531 units of 118 tiles: 177 us with two, 186 with three, 168 now).
+// A launch of fewer units than CUs keeps three, so that its units are cut at all: 234
+// units of 78 tiles take 76 us so and 83 uncut.
+inline int balance_groups(int d, int n_units, int n_cu) {
+  if (d != 64) return dense_groups_per_cu(d);
+  return n_units > n_cu ? 1 : dense_groups_per_cu(d);
+}
+
 inline void plan_dense_units(const DensePlanShape &s, const std::vector<HeadKV> &global,
                              const std::vector<HeadKV> &sink_dummy,
                              const std::vector<HeadKV> &cell_heads, int n_cu,
-                             std::vector<DenseUnit> &units, std::vector<CombineItem> &comb,
-                             int groups_per_cu = 2) {
+                             std::vector<DenseUnit> &units, std::vector<CombineItem> &comb) {
   const int L = s.L, nv = s.nv;
   const int nqt = (L + kQTile - 1) / kQTile;
   units.clear();
@@ -173,7 +186,7 @@ inline void plan_dense_units(const DensePlanShape &s, const std::vector<HeadKV> 
           }
         }
   }
-  balance_units(n_cu, units, comb, groups_per_cu);
+  balance_units(n_cu, units, comb, balance_groups(s.d, (int)units.size(), n_cu));
 }
 
 // ---------------------------------------------------------------------------
@@ -352,7 +365,7 @@ inline int first_unit_outside(const std::vector<DenseUnit> &units,
 // ---------------------------------------------------------------------------
 // Tail balancing of a dense launch.  Work groups are dealt round-robin to the
 // 8 XCDs and the kernel maps them so that XCD x runs a contiguous run of the
-// unit list in order, `groups_per_cu` per CU at a time (dense_groups_per_cu).  With equal units the
+// unit list in order, `groups_per_cu` per CU at a time (balance_groups).  With equal units the
 // last round of a run is partly empty.  For each run, the tail (its last
 // partial round, or that plus one full round) is cut into pieces of whole key
 // tiles when a list-scheduling simulation says the run then ends earlier; each

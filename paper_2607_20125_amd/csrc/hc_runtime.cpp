@@ -350,6 +350,7 @@ void plan_units(const hc_ctx *c, const Layer &l, int nv, std::vector<DenseUnit> 
     return out;
   };
   DensePlanShape shape;
+  shape.d = D;
   shape.L = c->L;
   shape.nv = nv;
   shape.g_parts = merged_anyway(c, l, nv) ? 0 : global_parts(D, c->L, nv);
@@ -363,8 +364,7 @@ void plan_units(const hc_ctx *c, const Layer &l, int nv, std::vector<DenseUnit> 
       c->cfg.spatial_cell > 0 ? parts(l.sp_heads, l.k_sp, l.v_sp, c->cells.keys)
                               : std::vector<HeadKV>{};
   plan_dense_units(shape, parts(l.g_heads, l.k_g, l.v_g, c->g_keys),
-                   parts(l.sd_heads, l.k_sd, l.v_sd, c->sd_keys), cell_heads, c->n_cu, units, comb,
-                   dense_groups_per_cu(D));
+                   parts(l.sd_heads, l.k_sd, l.v_sd, c->sd_keys), cell_heads, c->n_cu, units, comb);
 }
 
 template <class T>

@@ -419,8 +419,37 @@ static void wide_lists() {
   }
 }
 
+// 64-dim tails: the work per CU decides how long a launch takes (us for the layer with
+// three, two and one slot per CU: 186, 177 and 168).
+static void tails_64() {
+  struct { int L, nv, n_sd, n_g; } lists[] = {{7552, 1, 6, 3}, {8296, 7, 2, 1}, {4704, 5, 5, 2}, {5760, 2, 7, 1}};
+  for (auto &k : lists) {
+    double us[4];
+    for (int groups = 1; groups <= 3; ++groups) {
+      std::vector<HeadKV> g, sd;
+      for (int i = 0; i < k.n_g; ++i) g.push_back(HeadKV{i, fake_base(0, i * 64), fake_base(1, i * 64)});
+      for (int i = 0; i < k.n_sd; ++i) sd.push_back(HeadKV{k.n_g + i, fake_base(2, i * 64), fake_base(3, i * 64)});
+      DensePlanShape shape;
+      shape.d = 64; shape.L = k.L; shape.nv = k.nv;
+      std::vector<DenseUnit> units;
+      std::vector<CombineItem> comb;
+      plan_dense_units(shape, g, sd, {}, groups == 1 ? 256 : 0, units, comb);
+      if (groups > 1) balance_units(256, units, comb, groups);
+      us[groups] = dense_us(kCost64, (int)units.size(), 256, [&](int i, int, int *same) {
+        *same = 1;
+        return unit_tiles(units[i]);
+      });
+    }
+    CHECK(us[1] < 0.97 * us[3], "L %d nv %d heads %d/%d: estimates %.0f, %.0f, %.0f us", k.L, k.nv, k.n_g, k.n_sd,
+          us[1], us[2], us[3]);
+  }
+  CHECK(balance_groups(64, 256, 256) == 3 && balance_groups(64, 257, 256) == 1 && balance_groups(128, 257, 256) == 2,
+        "slots per CU");
+}
+
 int main() {
   wide_lists();
+  tails_64();
   slot_groups_match();
   static_choices();
   // the device-built work list of the no-allocation entry point
@@ -482,7 +511,8 @@ int main() {
       const bool expect = n_cu == 256 && ((ly.L == 4680 && ly.n_g == 2 && ly.n_sd == 0) ||
                                           (ly.L == 4680 && ly.n_g == 1 && ly.n_sd == 1));
       check_layer(ly, n_cu, expect);
-      check_layer(ly, n_cu, false, 3);   // three work groups per CU (64-dim heads)
+      check_layer(ly, n_cu, false, 3);   // 64-dim heads of fewer units than CUs
+      check_layer(ly, n_cu, false, 1);   // ... and of more
     }
   if (failures) {
     std::printf("plan_check: %d failures\n", failures);
