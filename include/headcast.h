@@ -71,7 +71,7 @@ typedef enum {
   HC_E_INVAL = -1,   /* bad argument: null pointer, bad layer, bad size, bad label   */
   HC_E_STATE = -2,   /* call not valid in the layer's current state                  */
   HC_E_ORDER = -3,   /* block index neither the current block nor the next one       */
-  HC_E_NOMEM = -4,   /* device allocation failed                                      */
+  HC_E_NOMEM = -4,   /* an allocation failed (device or host memory)                  */
   HC_E_DEVICE = -5   /* a HIP runtime call failed (message in hc_last_error)          */
 } hc_status;
 

@@ -12,6 +12,8 @@
 #include <cstdio>
 #include <cstring>
 #include <functional>
+#include <memory>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -107,10 +109,18 @@ hc_status fail(hc_ctx *c, hc_status s, const char *fmt, ...) {
     va_start(ap, fmt);
     vsnprintf(buf, sizeof buf, fmt, ap);
     va_end(ap);
-    c->err = buf;
+    try {
+      c->err = buf;
+    } catch (const std::bad_alloc &) {
+      c->err.clear();
+    }
   }
   return s;
 }
+
+// Ends the functions that allocate host memory: nothing is thrown across the ABI.
+#define HC_NO_HOST_MEMORY(ctx) \
+  catch (const std::bad_alloc &) { return fail(ctx, HC_E_NOMEM, "out of host memory"); }
 
 // A failed HIP call stays the thread's last error until it is read, and the next
 // launch would take it for its own: every failure that is reported or passed over
@@ -279,7 +289,7 @@ int64_t sp_split_rows(const hc_ctx *c, const Layer &l) {
 // they are written (hipFree waits for the device, and so does the other branch).
 // Six buffers and two work lists allocated, cleared and freed one by one left the
 // GPU idle for 1.4 ms (480P) to 1.9 ms (720P) of a layer's classification.
-hc_status install_types(hc_ctx *c, Layer &l, const uint8_t *types, hipStream_t s) {
+hc_status install_types(hc_ctx *c, Layer &l, const uint8_t *types, hipStream_t s) try {
   const int H = c->cfg.n_heads, D = c->cfg.head_dim;
   l.has_types = false;
   l.types.assign(types, types + H);
@@ -330,7 +340,7 @@ hc_status install_types(hc_ctx *c, Layer &l, const uint8_t *types, hipStream_t s
   if ((st = need_part(c, need, s)) != HC_OK) return st;
   l.has_types = true;
   return HC_OK;
-}
+} HC_NO_HOST_MEMORY(c)
 
 // Whether a layer-step has partials to merge however its Global heads are cut: those of
 // split Spatial heads, or of two-block Sink/Dummy heads.
@@ -377,7 +387,7 @@ hc_status upload(hc_ctx *c, DevBuf &b, const std::vector<T> &v) {
   return HC_OK;
 }
 
-hc_status ensure_plan(hc_ctx *c, Layer &l, int nv, hipStream_t s) {
+hc_status ensure_plan(hc_ctx *c, Layer &l, int nv, hipStream_t s) try {
   if (l.plan_nv == nv) return HC_OK;
   std::vector<DenseUnit> units;
   std::vector<CombineItem> comb;
@@ -435,7 +445,7 @@ hc_status ensure_plan(hc_ctx *c, Layer &l, int nv, hipStream_t s) {
   l.plan_nv = nv;
   l.plan_used = true;
   return HC_OK;
-}
+} HC_NO_HOST_MEMORY(c)
 
 ScatterArgs scatter_args(const hc_ctx *c, const Layer &l) {
   ScatterArgs a{};
@@ -700,7 +710,7 @@ int32_t hc_ring_slot(int64_t block, int32_t W) {
   return (int32_t)(1 + (block - 1) % (W - 1));
 }
 
-hc_status hc_create(const hc_config *cfg, int device, hc_ctx **out) {
+hc_status hc_create(const hc_config *cfg, int device, hc_ctx **out) try {
   if (!out) return HC_E_INVAL;
   *out = nullptr;
   if (hc_validate_config(cfg) != HC_OK) return HC_E_INVAL;
@@ -709,7 +719,8 @@ hc_status hc_create(const hc_config *cfg, int device, hc_ctx **out) {
   auto ok = [](hipError_t e) { return e == hipSuccess || ((void)hipGetLastError(), false); };
   if (!ok(hipGetDeviceCount(&ndev)) || device < 0 || device >= ndev) return HC_E_DEVICE;
   if (!ok(hipSetDevice(device)) || !ok(static_scratch(device, &scratch))) return HC_E_DEVICE;
-  hc_ctx *c = new hc_ctx;
+  std::unique_ptr<hc_ctx, void (*)(hc_ctx *)> owner(new hc_ctx, hc_destroy);
+  hc_ctx *c = owner.get();
   c->cfg = *cfg;
   c->device = device;
   c->scratch = scratch;
@@ -728,16 +739,11 @@ hc_status hc_create(const hc_config *cfg, int device, hc_ctx **out) {
                                  cfg->window_blocks, cfg->spatial_cell);
     hc_status st = upload(c, c->cell_off_d, c->cells.off);
     if (st == HC_OK) st = upload(c, c->qmap_d, c->cells.qmap);
-    if (st != HC_OK) {
-      free_buf(c->cell_off_d);
-      free_buf(c->qmap_d);
-      delete c;
-      return st;
-    }
+    if (st != HC_OK) return st;
   }
-  *out = c;
+  *out = owner.release();
   return HC_OK;
-}
+} HC_NO_HOST_MEMORY(nullptr)
 
 void hc_destroy(hc_ctx *c) {
   if (!c) return;
@@ -763,7 +769,7 @@ void hc_destroy(hc_ctx *c) {
 }
 
 hc_status hc_set_head_types(hc_ctx *c, int layer, const uint8_t *types, int64_t cur_block,
-                            const void *k_win, const void *v_win, hc_stream stream) {
+                            const void *k_win, const void *v_win, hc_stream stream) try {
   hc_status st = check_layer(c, layer);
   if (st != HC_OK) return st;
   if ((st = check_types(c, types)) != HC_OK) return st;
@@ -782,7 +788,7 @@ hc_status hc_set_head_types(hc_ctx *c, int layer, const uint8_t *types, int64_t 
   if ((st = split_window(c, l, cur_block, k_win, v_win, s)) != HC_OK) return st;
   l.cur_block = cur_block;
   return HC_OK;
-}
+} HC_NO_HOST_MEMORY(c)
 
 hc_status hc_get_layout(const hc_ctx *cc, int layer, int32_t *head_slot, int32_t *ring) {
   hc_ctx *c = const_cast<hc_ctx *>(cc);
@@ -802,7 +808,7 @@ hc_status hc_get_layout(const hc_ctx *cc, int layer, int32_t *head_slot, int32_t
 }
 
 hc_status hc_append_block(hc_ctx *c, int layer, int64_t block, const void *k_blk,
-                          const void *v_blk, hc_stream stream) {
+                          const void *v_blk, hc_stream stream) try {
   hc_status st = check_layer(c, layer);
   if (st != HC_OK) return st;
   if (!k_blk || !v_blk) return fail(c, HC_E_INVAL, "block pointers must not be NULL");
@@ -827,10 +833,10 @@ hc_status hc_append_block(hc_ctx *c, int layer, int64_t block, const void *k_blk
   if (st != HC_OK) return st;
   l.cur_block = block;
   return HC_OK;
-}
+} HC_NO_HOST_MEMORY(c)
 
 hc_status hc_attention(hc_ctx *c, int layer, const void *q, const uint8_t *head_types, float *o,
-                       hc_stream stream) {
+                       hc_stream stream) try {
   hc_status st = check_attention(c, layer, q, head_types, o);
   if (st != HC_OK) return st;
   Layer &l = c->layers[layer];
@@ -850,10 +856,10 @@ hc_status hc_attention(hc_ctx *c, int layer, const void *q, const uint8_t *head_
   wk.sp_part = (float *)c->sp_part.p;
   wk.sp_ml = (float *)c->sp_ml.p;
   return run_layer(c, l, nv, q, o, wk, (hipStream_t)stream);
-}
+} HC_NO_HOST_MEMORY(c)
 
 hc_status hc_attention_static(hc_ctx *c, int layer, const void *q, const uint8_t *head_types,
-                              float *o, hc_stream stream) {
+                              float *o, hc_stream stream) try {
   hc_status st = check_attention(c, layer, q, head_types, o);
   if (st != HC_OK) return st;
   if (c->cfg.spatial_cell > 0)
@@ -912,7 +918,7 @@ hc_status hc_attention_static(hc_ctx *c, int layer, const void *q, const uint8_t
   wk.shared_part = shared;
   HC_HIP(c, launch_static_plan(p, (DenseUnit *)wk.units, (CombineItem *)wk.comb, s));
   return run_layer(c, l, nv, q, o, wk, s);
-}
+} HC_NO_HOST_MEMORY(c)
 
 namespace {
 
@@ -940,7 +946,7 @@ uint8_t decide_label(const hc_config &cfg, const double *st) {
 
 hc_status hc_classify_heads(hc_ctx *c, int layer, int64_t cur_block, const void *q,
                             const void *k_win, const void *v_win, uint8_t *types_out,
-                            double *stats_out, hc_stream stream) {
+                            double *stats_out, hc_stream stream) try {
   hc_status st = check_layer(c, layer);
   if (st != HC_OK) return st;
   if (!q || !k_win || !v_win || !types_out)
@@ -1104,7 +1110,7 @@ hc_status hc_classify_heads(hc_ctx *c, int layer, int64_t cur_block, const void 
   std::memcpy(types_out, labels.data(), H);
   c->cls_done = true;
   return HC_OK;
-}
+} HC_NO_HOST_MEMORY(c)
 
 hc_status hc_classify_outputs(hc_ctx *c, int which, float *dst, hc_stream stream) {
   if (!c) return HC_E_INVAL;
@@ -1141,7 +1147,7 @@ hc_status hc_profile_enable(hc_ctx *c, int on) {
   return HC_OK;
 }
 
-hc_status hc_profile_read(hc_ctx *c, int kind, double *total_ms, int64_t *launches) {
+hc_status hc_profile_read(hc_ctx *c, int kind, double *total_ms, int64_t *launches) try {
   if (!c || kind < 0 || kind >= HC_K_COUNT || !total_ms || !launches) return HC_E_INVAL;
   HC_HIP(c, hipSetDevice(c->device));
   for (int k = 0; k < HC_K_COUNT; ++k) {
@@ -1164,6 +1170,6 @@ hc_status hc_profile_read(hc_ctx *c, int kind, double *total_ms, int64_t *launch
   c->prof_ms[kind] = 0;
   c->prof_n[kind] = 0;
   return HC_OK;
-}
+} HC_NO_HOST_MEMORY(c)
 
 }  // extern "C"

@@ -10,6 +10,7 @@
 #include <cstdlib>
 #include <cstring>
 #include <map>
+#include <new>
 #include <string>
 #include <vector>
 
@@ -29,6 +30,12 @@ inline std::vector<std::string> faults;
 inline hipError_t last = hipSuccess;
 inline int fail_malloc_in = 0;        // n: the n-th hipMalloc from now fails
 inline hipError_t fail_memcpy = hipSuccess;   // the next hipMemcpy fails with this
+inline int fail_new_in = 0;           // n: the n-th host allocation from now throws
+inline int quiet = 0;                 // > 0: not the runtime's own allocations
+struct Quiet {
+  Quiet() { ++quiet; }
+  ~Quiet() { --quiet; }
+};
 inline int launches = 0, syncs = 0;
 inline bool dense_wide = false;       // of the last dense launch
 inline int dense_units = 0;           // its units with work
@@ -42,7 +49,7 @@ inline hipError_t take_last() {
   last = hipSuccess;
   return e;
 }
-inline void fault(const std::string &what) { faults.push_back(what); }
+inline void fault(const std::string &what) { faults.push_back(what); }   // (under a Quiet)
 
 // base of the live allocation that holds [p, p + bytes), or null
 inline void *owner(const void *p, size_t bytes) {
@@ -54,6 +61,7 @@ inline void *owner(const void *p, size_t bytes) {
 }
 
 inline void touch(const char *what, const void *p, size_t bytes, hipStream_t s, bool write) {
+  Quiet q;
   void *base = owner(p, bytes);
   if (!base) {
     char buf[160];
@@ -67,6 +75,7 @@ inline void touch(const char *what, const void *p, size_t bytes, hipStream_t s, 
 }
 
 inline void done(hipStream_t s) {
+  Quiet q;
   std::vector<Write> left;
   for (const Write &w : pending)
     if (w.stream != s) left.push_back(w);
@@ -75,14 +84,25 @@ inline void done(hipStream_t s) {
 
 }  // namespace fake
 
+void *operator new(size_t n) {
+  if (fake::quiet == 0 && fake::fail_new_in > 0 && --fake::fail_new_in == 0) throw std::bad_alloc();
+  void *p = std::malloc(n ? n : 1);
+  if (!p) throw std::bad_alloc();
+  return p;
+}
+void operator delete(void *p) noexcept { std::free(p); }
+void operator delete(void *p, size_t) noexcept { std::free(p); }
+
 extern "C" {
 hipError_t hipMalloc(void **p, size_t n) {
+  fake::Quiet q;
   if (fake::fail_malloc_in > 0 && --fake::fail_malloc_in == 0) return fake::ret(hipErrorOutOfMemory);
   *p = std::aligned_alloc(256, (n + 255) / 256 * 256);
   fake::live[(uintptr_t)*p] = n;
   return hipSuccess;
 }
 hipError_t hipFree(void *p) {
+  fake::Quiet q;
   fake::pending.clear();                      // waits for the device
   if (!p) return hipSuccess;
   if (!fake::live.erase((uintptr_t)p)) fake::fault("hipFree of memory that is not allocated");
@@ -191,6 +211,7 @@ hipError_t launch_cls_reduce(const ClsReduceArgs &a, hipStream_t s) {
   return fake::take_last();
 }
 hipError_t static_scratch(int, void **p) {
+  fake::Quiet q;
   static void *mem = nullptr;
   if (!mem) {
     mem = std::aligned_alloc(256, kStaticScratchBytes);

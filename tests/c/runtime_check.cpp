@@ -178,11 +178,67 @@ void small_windows() {
     }
 }
 
+// No call lets a failed host allocation out: it returns HC_E_NOMEM, and the context
+// works on.  (The checks' own vectors are made outside the calls.)
+void host_memory() {
+  std::vector<uint8_t> labels(4);
+  auto failing = [&](const char *what, int nth, auto &&call) -> bool {   // false: no allocation failed
+    fake::fail_new_in = nth;
+    hc_status st = HC_OK;
+    bool threw = false;
+    try {
+      st = call();
+    } catch (const std::bad_alloc &) {
+      threw = true;
+    }
+    const bool failed = fake::fail_new_in == 0;
+    fake::fail_new_in = 0;
+    CHECK(!threw, "%s: allocation %d thrown across the ABI", what, nth);
+    CHECK(st == HC_OK || st == HC_E_NOMEM, "%s: status %d", what, st);
+    return failed;
+  };
+  hc_config cfg = config(2, 4);
+  for (int cell = 0; cell <= 4; cell += 4) {
+    cfg.spatial_cell = cell;
+    for (int nth = 1;; ++nth) {
+      hc_ctx *c = nullptr;
+      const bool more = failing("hc_create", nth, [&] { return hc_create(&cfg, 0, &c); });
+      hc_destroy(c);
+      if (!more) break;
+    }
+  }
+  cfg.spatial_cell = 0;
+  enum { kSet, kAttend, kStatic, kAppend, kClassify, kCalls };
+  const char *names[] = {"hc_set_head_types", "hc_attention", "hc_attention_static", "hc_append_block", "hc_classify_heads"};
+  int n[kCalls] = {};
+  for (int call = 0; call < kCalls; ++call)
+    for (int nth = 1; nth < 400; ++nth) {
+      Ctx x(cfg);
+      CHECK(x.set(0, kFew) == HC_OK && x.attend(0, kFew) == HC_OK && x.set(1, kMany) == HC_OK, "%s", hc_last_error(x.c));
+      const bool more = failing(names[call], nth, [&] {
+        switch (call) {
+          case kSet: return x.set(1, kFew);
+          case kAttend: return x.attend(1, kMany);
+          case kStatic: return x.attend_static(1, kMany);
+          case kAppend: return x.append(1);
+          default: return x.classify(1, labels);
+        }
+      });
+      n[call] += more;
+      CHECK(x.attend(0, kFew) == HC_OK, "layer 0 after allocation %d of %s: %s", nth, names[call], hc_last_error(x.c));
+      CHECK(x.set(1, kFew) == HC_OK && x.attend(1, kFew) == HC_OK, "layer 1 again: %s", hc_last_error(x.c));
+      if (!more) break;
+    }
+  CHECK(n[kSet] > 0 && n[kAttend] > 0 && n[kClassify] > 0, "allocations: %d %d %d", n[kSet], n[kAttend], n[kClassify]);
+  CHECK(n[kStatic] == 0, "hc_attention_static allocates host memory (%d)", n[kStatic]);
+}
+
 struct { const char *name; void (*run)(); } checks[] = {
     {"errors_are_reported_once", errors_are_reported_once},
     {"shared_buffers_after_failed_growth", shared_buffers_after_failed_growth},
     {"first_attention_on_another_stream", first_attention_on_another_stream},
     {"small_windows", small_windows},
+    {"host_memory", host_memory},
 };
 
 }  // namespace

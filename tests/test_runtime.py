@@ -29,7 +29,7 @@ def runtime_check(tmp_path_factory):
 
 
 @pytest.mark.parametrize("check", ["errors_are_reported_once", "shared_buffers_after_failed_growth",
-                                   "first_attention_on_another_stream", "small_windows"])
+                                   "first_attention_on_another_stream", "small_windows", "host_memory"])
 def test_runtime(runtime_check, check):
     run = subprocess.run([runtime_check, check], capture_output=True, text=True, timeout=120,
                          env=dict(os.environ, ASAN_OPTIONS="detect_leaks=0"))
