@@ -25,10 +25,12 @@ using namespace dev;
 // builtins into one file or the other (AGPRs for this source, whose build leaves
 // out the VGPR form the others use), and with scores in AGPRs every one is
 // copied out; so the score products are inline assembly with the file in the
-// constraint.  The compiler knows nothing of their latency: no vector
-// instruction touches a score before ten more slots are issued or `settle` has
-// waited, and a probability is packed at least one slot before the product that
-// reads it.
+// constraint.  The compiler knows nothing of their latency: the source has no vector
+// instruction touch a score before ten more slots are issued or `settle` has
+// waited, and packs a probability at least one slot before the product that
+// reads it.  The compiler may still copy scores ahead of `settle` (it does, behind
+// the last products of a partial step, 20 wait states after the nearest), so
+// tests/test_dense128_scores.py walks the built instructions from every such product.
 //
 // One wave per SIMD has nobody to hide behind, so the order is written out: a
 // step is 32 slots of two products each (16 of S(t+1) = K(t+1) Q^T, 16 of O +=
@@ -37,8 +39,9 @@ using namespace dev;
 // fences keep it.  The softmax of tile t+1 begins in the last slots of PV(t), so
 // every slot has the same vector work.  Both exp2 between the two products
 // measured best: one between and one after 5% slower, both after 6%.  The only
-// barrier of a step sits between its two halves, where the operand reads of
-// the second half are already under way; the DMA of K(t+3) and V(t+2) follows
+// barrier of a step sits between its two halves; the first operand reads of the
+// second half are issued before it, but it waits for them too (__syncthreads drains
+// the LDS counter).  The DMA of K(t+3) and V(t+2) follows
 // it four instructions at a time (all at once, two or one at a time: 0.5-2% slower).
 // ---------------------------------------------------------------------------
 constexpr int kPre = 6;      // pairs of the next tile formed during PV: 5 would leave the
