@@ -232,12 +232,12 @@ hc_status hc_append_block(hc_ctx *ctx, int layer, int64_t block, const void *k_b
  *   head_types : host uint8 [H]; must equal the layer's table (else HC_E_STATE)
  *   o : float32 [H][L][d] (device), every head written in place.
  * Launches the grouped work of the layer: every Global head is cut into one
- * work unit per window block and every Sink/Dummy head into one unit, each
- * unit 128 queries wide, so all units of the dense kernel cost the same; the
- * per-block partial results of Global heads are merged by a combine kernel;
- * Spatial heads run on the windowed kernel (when they give too few work groups
- * to fill the GPU, their key frames are cut into ranges whose partial results
- * a merge kernel combines).  Async. */
+ * work unit per window block (small windows stay whole) and every Sink/Dummy head
+ * into one unit (per block), each unit 128 queries wide, and the last units of the
+ * list into pieces where that ends the launch earlier; partial results of cut
+ * heads are merged by a further launch.  Spatial heads run on the windowed kernel
+ * (when they give too few work groups to fill the GPU, their key frames are cut
+ * into ranges whose partial results the same launch merges).  Async. */
 hc_status hc_attention(hc_ctx *ctx, int layer, const void *q, const uint8_t *head_types,
                        float *o, hc_stream stream);
 
@@ -275,7 +275,9 @@ hc_status hc_memory_bytes(const hc_ctx *ctx, int64_t *bytes);
 /* Kernel timing: when enabled, every launch the context makes records a pair
  * of HIP events on the stream it is launched on.  hc_profile_read synchronises
  * those events and returns the summed duration (ms) and the launch count of
- * one kernel kind since the last reset, then resets it. */
+ * one kernel kind since the last reset, then resets it.  A merge of partials
+ * counts as HC_K_COMBINE; one of Spatial ranges alone is timed with its
+ * HC_K_SPATIAL launch. */
 enum { HC_K_DENSE = 0, HC_K_SPATIAL = 1, HC_K_SCATTER = 2, HC_K_STATS = 3, HC_K_COMBINE = 4,
        HC_K_COUNT = 5 };
 hc_status hc_profile_enable(hc_ctx *ctx, int on);

@@ -213,7 +213,9 @@ __global__ __launch_bounds__(256) void cls_stats_kernel(StatsArgs a) {
 // would fall into one bin there and its LDS atomics would queue up, and usually
 // two counting passes settle the rest.  Measured with 12 heads: L = 10800 in 340
 // -> 38 us, L = 4680 in 235 -> 26 us, against 16 passes of 8-bit digits by 256
-// threads over cosines 32 bytes apart.
+// threads over cosines 32 bytes apart.  1024 threads leave 128 registers each, so 44
+// values (the sums above all, which only the last lines use) are kept in scratch
+// memory meanwhile.
 // ---------------------------------------------------------------------------
 constexpr int kRedThreads = 1024;
 constexpr int kDigit = 11, kBins = 1 << kDigit;

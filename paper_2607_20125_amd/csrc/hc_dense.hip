@@ -11,8 +11,9 @@ using namespace dev;
 // ---------------------------------------------------------------------------
 // Dense kernel: one work group = kQTile (128) queries of one unit on 4 waves of
 // 32 queries; two work groups share a CU (two waves per SIMD, 2 x 80 KB of LDS;
-// three with 64-dim heads, 40 KB and 168 registers each), so one group's barrier
-// waits and softmax overlap the others' matrix work.  With 64-dim heads a tile has
+// three with 64-dim heads, 40 KB and 168 registers each, six more in scratch memory
+// outside the key loops), so one group's barrier waits and softmax overlap the others'
+// matrix work.  With 64-dim heads a tile has
 // half the products for the same softmax, and the third wave per SIMD overlaps them.
 // K/V tiles of 64 keys are fetched kDist tiles ahead of use (K ring of kDist,
 // V ring of kDist + 1 buffers); one barrier per tile.

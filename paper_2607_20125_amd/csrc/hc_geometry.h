@@ -69,9 +69,10 @@ inline int spatial_split_count(int64_t groups, int64_t resident, int64_t frames)
 // of the same row and halo rows outside the frame (at most rows_per_step - 1
 // of them, in a step that also holds a row inside) from the neighbouring frame
 // or the lead; all such keys are masked by index, so only the storage size
-// matters.  `y0`, `x0` place the frame inside its storage (no margins).
+// matters.  There are no margins: rows == grid_h, and a frame starts at row 0 and
+// column 0 of its storage, which the scatter's walk relies on.
 struct SpatialGeom {
-  int32_t rows, pitch, y0, x0;
+  int32_t rows, pitch;
   int64_t lead;
 };
 
@@ -79,8 +80,6 @@ inline SpatialGeom spatial_geometry(const hc_config &cfg) {
   SpatialGeom g{};
   g.rows = cfg.grid_h;
   g.pitch = (cfg.grid_w + 7) / 8 * 8;
-  g.y0 = 0;
-  g.x0 = 0;
   const int rps = std::max(spatial_rows_per_step(cfg.spatial_radius),
                            spatial_rows_per_step(cfg.proxy_radius));
   g.lead = (int64_t)(rps - 1) * g.pitch;

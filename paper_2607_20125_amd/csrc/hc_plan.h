@@ -8,7 +8,6 @@
 
 #include <algorithm>
 #include <cstdint>
-#include <functional>
 #include <vector>
 
 #include "hc_units.h"
@@ -378,21 +377,6 @@ namespace plan_detail {
 constexpr double kUnitOverheadTiles = 4.0;   // fixed cost of a unit (Q load, fill, store)
 constexpr int kMinPieceTiles = 12;
 constexpr int kMaxPieces = 8;
-
-// End time of a whole run, by the standard library's heap (the CPU checks hold
-// the plans against it).
-inline double run_makespan(const std::vector<double> &cost, int slots) {
-  std::vector<double> heap(slots, 0.0);   // min-heap of slot free times
-  std::make_heap(heap.begin(), heap.end(), std::greater<double>());
-  double end = 0.0;
-  for (double w : cost) {
-    std::pop_heap(heap.begin(), heap.end(), std::greater<double>());
-    heap.back() += w;
-    end = std::max(end, heap.back());
-    std::push_heap(heap.begin(), heap.end(), std::greater<double>());
-  }
-  return end;
-}
 
 // Free times of an XCD's work-group slots: each added unit goes to the slot that
 // is free first.  A copy continues from the same state.

@@ -19,16 +19,17 @@ constexpr int kKTile = 64;     // keys per dense KV tile
 
 // Work groups of the dense kernels that share a CU: two of the 128-dim heads' by
 // their 80 KB rings (and their two waves of up to 512 registers, one per SIMD);
-// 64-dim heads need half the LDS and 168 registers, so three (four would need 128).
+// 64-dim heads need half the LDS, and three fit in 168 registers with six kept in
+// scratch memory, outside the key loops (four would need 128).
 inline constexpr int dense_groups_per_cu(int d) { return d == 64 ? 3 : 2; }
 
 // One dense work unit: kQTile queries of one head against the contiguous key range
 // [kv0, kv1) of a [keys][d] K buffer and its 8-key-grouped V buffer
-// ([keys/8][d][8]).  Every unit covers at most one window block of keys, so all
-// units cost about the same; a Global head's window is split into one unit per
-// block and the per-block partial results are merged by the combine kernel.
-// The units of a launch's last round may be cut further into pieces of whole
-// key tiles (hc_plan.h).
+// ([keys/8][d][8]).  A Global head's window is split into one unit per block, whose
+// partial results are merged (so units cost about the same); small windows stay whole,
+// and the no-allocation call may cut them into other equal runs of key tiles.  The
+// units of a launch's last round may be cut further into pieces of whole key tiles
+// (hc_plan.h).
 struct DenseUnit {
   const uint16_t *k;
   const uint16_t *v;

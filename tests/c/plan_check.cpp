@@ -7,6 +7,7 @@
 #include <cmath>
 #include <cstdio>
 #include <cstdlib>
+#include <functional>
 #include <map>
 #include <set>
 #include <tuple>
@@ -26,6 +27,20 @@ static int failures = 0;
       if (++failures > 20) std::exit(1);                   \
     }                                                      \
   } while (0)
+
+// End time of a whole run, by the standard library's heap.
+static double run_makespan(const std::vector<double> &cost, int slots) {
+  std::vector<double> heap(slots, 0.0);   // min-heap of slot free times
+  std::make_heap(heap.begin(), heap.end(), std::greater<double>());
+  double end = 0.0;
+  for (double w : cost) {
+    std::pop_heap(heap.begin(), heap.end(), std::greater<double>());
+    heap.back() += w;
+    end = std::max(end, heap.back());
+    std::push_heap(heap.begin(), heap.end(), std::greater<double>());
+  }
+  return end;
+}
 
 struct Layer {
   int L, nv, n_g, n_sd, n_cell_units;
@@ -158,7 +173,7 @@ static void check_layer(const Layer &ly, int n_cu, bool expect_cut, int groups =
       std::vector<double> cost;
       for (int i = b; i < e; ++i)
         if (us[i].head >= 0) cost.push_back(unit_tiles(us[i]) + plan_detail::kUnitOverheadTiles);
-      worst = std::max(worst, plan_detail::run_makespan(cost, slots));
+      worst = std::max(worst, run_makespan(cost, slots));
     }
     return worst;
   };
@@ -313,7 +328,7 @@ static void slot_groups_match() {
       const int n = 1 + rnd(200);
       g.add(c, n);
       cost.insert(cost.end(), n, c);
-      CHECK(g.end == plan_detail::run_makespan(cost, slots), "%d slots: %f", slots, g.end);
+      CHECK(g.end == run_makespan(cost, slots), "%d slots: %f", slots, g.end);
     }
     int held = 0;
     for (int i = 0; i < g.groups; ++i) held += g.n[i];
