@@ -260,10 +260,8 @@ hc_status need_part(hc_ctx *c, int64_t slots, hipStream_t s) {
   HC_HIP(c, hipDeviceSynchronize());
   c->part_slots = 0;
   hc_status st = alloc_zero(c, c->part, (size_t)slots * partial_floats(c->cfg.head_dim) * 4, s);
-  if (st != HC_OK) return st;
-  HC_HIP(c, hipStreamSynchronize(s));      // the next layer to use it may be on another stream
-  c->part_slots = slots;
-  return HC_OK;
+  if (st == HC_OK) c->part_slots = slots;
+  return st;
 }
 
 hc_status need_sp_part(hc_ctx *c, int64_t rows, hipStream_t s) {
@@ -272,10 +270,8 @@ hc_status need_sp_part(hc_ctx *c, int64_t rows, hipStream_t s) {
   c->sp_part_rows = 0;
   hc_status st = alloc_zero(c, c->sp_part, (size_t)rows * c->cfg.head_dim * 4, s);
   if (st == HC_OK) st = alloc_zero(c, c->sp_ml, (size_t)rows * 2 * 4, s);
-  if (st != HC_OK) return st;
-  HC_HIP(c, hipStreamSynchronize(s));
-  c->sp_part_rows = rows;
-  return HC_OK;
+  if (st == HC_OK) c->sp_part_rows = rows;
+  return st;
 }
 
 int64_t sp_split_rows(const hc_ctx *c, const Layer &l) {
