@@ -424,7 +424,9 @@ def measure(workload, args, primary):
             "peak": PEAK_HBM_GBS, "unit": "GB/s", "frac": round(gbs / PEAK_HBM_GBS, 4),
             "traffic": measured_traffic(workload, "spatial"),
             "avg_launch_ms": round(sp_ms, 4), "compulsory_bytes_per_launch": sp_by,
-            "tflops_algorithmic": round(sp_fl / (sp_ms * 1e-3) / 1e12, 2)}
+            "tflops_algorithmic": round(sp_fl / (sp_ms * 1e-3) / 1e12, 2),
+            "note": "the launch without the merge of its splits where the layer merges "
+                    "dense partials too (that launch is counted in combine)"}
         kv = counter_profile(workload, "spatial")
         if kv is not None:
             # matrix work the kernel issues (SQ_INSTS_MFMA x 32768 flops) over the
