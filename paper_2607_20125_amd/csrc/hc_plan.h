@@ -657,14 +657,14 @@ inline bool dense_wide_waves(int64_t tiles, int n_cu) {
 }
 
 // The same for a list as it is launched: 200 against 208 us for 8 Global heads of six
-// blocks of 2856 tokens, whose cut tails end unevenly.  Tail-balanced lists of 150 tiles
-// per group or more are not estimated (3-20 us): all 30 drawn ones ran in 0.94-1.00 of
-// the time.
+// blocks of 2856 tokens, whose cut tails end unevenly.  Tail-balanced lists of 120 tiles
+// per group or more are not estimated (3-20 us, which a classification waits for): all
+// 39 drawn ones ran in 0.94-1.01 of the time.
 inline bool dense_wide_waves(const std::vector<DenseUnit> &units, int n_cu, bool balanced) {
   int64_t tiles = 0;
   for (const DenseUnit &u : units) tiles += unit_tiles(u);
   if (!dense_wide_waves(tiles, n_cu)) return false;
-  if (!dense_us_covers(n_cu) || (balanced && tiles >= (int64_t)150 * dense_groups_per_cu(128) * n_cu))
+  if (!dense_us_covers(n_cu) || (balanced && tiles >= (int64_t)120 * dense_groups_per_cu(128) * n_cu))
     return true;
   auto tiles_of = [&](int i, int e, int *same) {
     const int nt = unit_tiles(units[i]);
