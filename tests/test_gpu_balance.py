@@ -93,3 +93,29 @@ def test_static_key_ranges_480p(hc, types):
     ctx.attention_static(0, q, types, got)
     torch.cuda.synchronize()
     assert_close(got.cpu().numpy(), ref.cpu().numpy().astype(np.float64), f"ranges {types.tolist()}")
+
+
+@pytest.mark.parametrize("d, grid, frames, nv, n_sd, n_g", [
+    (128, (30, 52), 3, 7, 0, 3),    # four ranges of seven blocks, 64 queries per wave
+    (128, (30, 52), 3, 2, 8, 4),    # one per block, 32 queries per wave although the list is long
+    (128, (23, 40), 3, 5, 4, 4),    # four ranges of five blocks, 32 queries per wave
+    (64, (30, 52), 3, 7, 7, 3),     # six ranges of seven blocks
+    (64, (30, 52), 3, 1, 0, 4),     # a single block in three ranges
+    (64, (20, 22), 1, 7, 0, 16),    # ranges of 12 and 13 tiles, the last one ragged
+])
+def test_static_choices(hc, d, grid, frames, nv, n_sd, n_g):
+    """The no-allocation call against hc_attention where it takes other key ranges or
+    another kernel (the counts are the planner's for these shapes)."""
+    import torch
+    types = np.array([0, 1] * (n_sd // 2) + [1] * (n_sd % 2) + [3] * n_g, np.uint8)
+    w = S.Workload("choice", 1, len(types), d, grid[0], grid[1], frames, 7, 4, 2, 485, (0, 0, 0, len(types)))
+    ctx = hc.Context(hc.config_from_workload(w), 0)
+    dev = torch.device("cuda:0")
+    shape = (w.n_heads, nv * w.block_tokens, d)
+    ctx.set_head_types(0, types, nv - 1, S.device_normal_bf16(shape, 1, dev), S.device_normal_bf16(shape, 2, dev))
+    q = S.device_normal_bf16((w.n_heads, w.block_tokens, d), 3, dev)
+    ref, got = out_tensor(w), out_tensor(w)
+    ctx.attention(0, q, types, ref)
+    ctx.attention_static(0, q, types, got)
+    torch.cuda.synchronize()
+    assert_close(got.cpu().numpy(), ref.cpu().numpy().astype(np.float64), f"choice d={d} {grid} nv={nv} {n_sd}+{n_g}")
